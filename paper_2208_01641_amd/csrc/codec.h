@@ -41,6 +41,8 @@ struct LayerGPU {
     PhaseDesc* d_ph = nullptr;
     uint8_t* d_w = nullptr;            // packed weights (float, bf16 or e4m3)
     uint16_t* d_wx = nullptr;          // FP32 GDN layers: the same as three bf16 parts (ConvArgs::wx)
+    uint8_t* d_wt = nullptr;           // weights in fragment order (ConvArgs::wt)
+    uint16_t* d_gt = nullptr;          // gamma in fragment order (ConvArgs::gt)
     float* d_bias = nullptr;
     float* d_rscale = nullptr;         // e4m3 form: per packed row, weight scale x input scale
     uint16_t* d_gsplit = nullptr;      // gamma as bf16 parts (layout in ConvArgs::gsplit)
@@ -54,6 +56,7 @@ struct LayerGPU {
 constexpr float kActQ = 8.0f;
 uint8_t e4m3_rne(float f);
 std::vector<uint16_t> gdn_gamma_split(const std::vector<double>& gamma, int co);
+std::vector<uint16_t> gdn_gamma_tiles(const std::vector<uint16_t>& gsplit, int co, int parts);
 
 struct Geo {
     int Hin, Win, Hg, Wg, s_in, Hout, Wout, s_out;

@@ -58,6 +58,7 @@ struct PhaseDesc {
     int32_t pad_;
     int64_t woff;            // element offset of this phase's packed weights
                              // [ntaps][CoP][CIN] from ConvArgs::w
+    int64_t wtoff;           // byte offset of its fragment-order weights from ConvArgs::wt
     int8_t dy[32], dx[32];   // tap offsets: input = s_in * grid + (dy, dx)
 };
 
@@ -69,6 +70,9 @@ struct ConvArgs {
     const void* w;           // packed weights of every phase (float, bf16 or e4m3)
     const void* wx;          // the same as bf16 parts for DT_F32X (or null): per 8 channels
                              // [part 0 x8][part 1 x8][part 2 x8], offsets 3 x those of w
+    const void* wt;          // weights in fragment order (or null), see tile_order in packing.h
+    const void* gt;          // gamma in fragment order (or null): [p][mt][part][lane][8] bf16, the
+                             // parts of gamma[16 mt + lane%16][(2p + i/4) 16 + 4 (lane/16) + i%4]
     const void* zero;        // >= 64 zero bytes: the source of out-of-image reads
     const float* bias;       // [CoP]
     const float* mu_in;      // LD_I8 offsets [CIN]

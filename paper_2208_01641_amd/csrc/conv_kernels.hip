@@ -28,11 +28,10 @@
 // The other forms keep that arrangement with 32 channels per chunk (bf16,
 // split-FP32) or 128 (tap, channel) pairs (e4m3).
 //
-// Data movement: the GDN layers of whole frames stage each K chunk's weight
-// tile once per block in an LDS ring (from registers, or for split-FP32 with
-// two pixel tiles per wave straight from global memory into LDS) and the
-// gamma slices of the epilogue likewise; pixels stay in per-wave register
-// rings.  The stride-1 output layer stages halo tiles (a block's rows of
+// Data movement: the GDN layers of whole frames are in gdn_kernels.hip; of
+// them only the image layer runs here (split-FP32: each K chunk's weight tile
+// goes through an LDS ring, and the gamma slices of the epilogue likewise).
+// The stride-1 output layer stages halo tiles (a block's rows of
 // pixels with a one-pixel border) and the weights in LDS per channel slice.
 // Small grids split K over the waves of a block with a fixed-order LDS
 // reduction.
@@ -43,137 +42,9 @@
 #include "../../include/lic.h"
 #include "conv_args.h"
 #include "kernels.h"
+#include "mfma_common.h"
 
 namespace lic {
-
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f4 mfma16x16x4(float a, float b, f4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// Operand precision of the convolution GEMM (accumulation is always FP32).
-//   DT_F32 : v_mfma_f32_16x16x4_f32, 16-channel K chunks, 4 channels per lane
-//   DT_BF16: v_mfma_f32_16x16x32_bf16, 32-channel K chunks, 8 channels per
-//            lane (one 16-byte load); activations between layers are stored
-//            as bf16, GDN / IGDN and all epilogue arithmetic stay FP32.
-template <int DT> struct Prec;
-// Frag: weight (A) fragment of one lane and K chunk; BIn: pixel (B) values
-// as loaded from NHWC activations; BFrag: B as fed to the matrix cores;
-// Elem / WElem: activation / weight element; WMUL: weight elements per
-// weight value.
-template <> struct Prec<DT_F32> {
-    using Frag = f4;
-    using Elem = float;
-    using WElem = float;
-    using BIn = f4;
-    using BFrag = f4;
-    static constexpr int KCH = 16, KE = 4, WMUL = 1;
-};
-template <> struct Prec<DT_BF16> {
-    using Frag = bf16x8;
-    using Elem = __bf16;
-    using WElem = __bf16;
-    using BIn = bf16x8;
-    using BFrag = bf16x8;
-    static constexpr int KCH = 32, KE = 8, WMUL = 1;
-};
-//   DT_F32X: FP32 operands split exactly into three bf16 parts (each rounded
-//            to nearest from what the previous parts leave: v = v0 + v1 + v2
-//            up to 2^-27 |v|); the products of parts i + j <= 2 run on
-//            v_mfma_f32_16x16x32_bf16 (each exact in FP32) with FP32
-//            accumulation, so a product carries a relative error near
-//            2^-25, the level of FP32 rounding.  Weights are split on the host
-//            ([part][8] per 8 channels), activations stay FP32 and are split
-//            when a chunk is used.
-struct Split3 {
-    bf16x8 p[3];
-};
-struct F32x8 {
-    f4 lo, hi;
-};
-template <> struct Prec<DT_F32X> {
-    using Frag = Split3;
-    using Elem = float;
-    using WElem = __bf16;
-    using BIn = F32x8;
-    using BFrag = Split3;
-    static constexpr int KCH = 32, KE = 8, WMUL = 3;
-};
-//   DT_FP8 : v_mfma_scale_f32_16x16x128_f8f6f4 on OCP e4m3 operands (unit
-//            block scales), K walked over the flattened (tap, channel) axis in
-//            chunks of 128: lane group g takes 32 consecutive channels of one
-//            tap (channels per tap are a multiple of 32).  Weights carry a
-//            per-row FP32 scale and activations are stored as e4m3(q x) with
-//            a per-layer q, both undone in the epilogue; the operands come
-//            from e4m3 activations only (the image layer and g_s's first and
-//            last layers of that form run on bf16 operands).
-template <> struct Prec<DT_FP8> {
-    using Frag = i32x8;
-    using Elem = uint8_t;
-    using WElem = uint8_t;
-    using BIn = i32x8;
-    using BFrag = i32x8;
-    static constexpr int KCH = 128, KE = 32, WMUL = 1;
-};
-
-// eight FP32 values as G bf16 parts, each rounded to nearest (v_cvt_pk_bf16_f32,
-// two values per instruction) from what the previous parts leave, which is
-// exact in FP32: v = v0 + ... + v_{G-1} up to the rounding of the last part
-template <int G>
-__device__ __forceinline__ void split_parts(const float (&v)[8], bf16x8 (&out)[G])
-{
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-    u32x4 w[G];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        f2 r = {v[2 * j], v[2 * j + 1]};
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const b2 h = __builtin_convertvector(r, b2);
-            w[g][j] = __builtin_bit_cast(uint32_t, h);
-            if (g + 1 < G) r -= __builtin_convertvector(h, f2);
-        }
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) out[g] = __builtin_bit_cast(bf16x8, w[g]);
-}
-
-// eight FP32 values as three bf16 parts (v = v0 + v1 + v2 up to 2^-27 |v|)
-__device__ __forceinline__ Split3 split3(const float (&v)[8])
-{
-    Split3 s;
-    split_parts<3>(v, s.p);
-    return s;
-}
-
-// e4m3 code of two floats in the low 16 bits, saturated to +-448 first
-__device__ __forceinline__ uint32_t e4m3x2(float lo, float hi)
-{
-    lo = fminf(fmaxf(lo, -448.0f), 448.0f);
-    hi = fminf(fmaxf(hi, -448.0f), 448.0f);
-    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(lo, hi, 0, false) & 0xffffu;
-}
-
-// unit E8M0 block scale (2^0) of the scaled MFMA
-constexpr int kE8M0One = 127;
-
-// Blocks are dispatched round-robin over the 8 XCDs (block L goes to XCD
-// L % 8).  Give each XCD a contiguous range of logical tiles so that tiles
-// sharing input halos and weights share one L2.
-__device__ __forceinline__ int xcd_logical_tile(int L, int T)
-{
-    const int xcd = L & 7, slot = L >> 3;
-    int prefix = 0;
-    for (int q = 0; q < xcd; ++q) prefix += (T + 7 - q) >> 3;
-    return prefix + slot;
-}
 
 // TAG is the layer id: it changes no code but gives every layer its own
 // kernel symbol, so profiles attribute time per layer.
@@ -181,13 +52,12 @@ __device__ __forceinline__ int xcd_logical_tile(int L, int T)
 // output tile and take interleaved K chunks; their partial sums are added in
 // LDS in the fixed wave order 0, 1, ..., KSPLIT-1, so results do not depend
 // on timing, batch size or which stream runs the kernel.
-// The split-FP32 kernels and the e4m3 GDN kernels on e4m3 activations are
-// built for two blocks (two waves per SIMD, 256 registers):
-// without the bound the compiler's split between VGPRs and accumulation
-// registers would take more than 256 in total.
+// The split-FP32 kernels are built for two blocks (two waves per SIMD, 256
+// registers): without the bound the compiler's split between VGPRs and
+// accumulation registers would take more than 256 in total.
 template <int TAG, int CIN, int MT, int NT, int WAVES, int KSPLIT, int LD, int EP, int DT>
 __global__ void __launch_bounds__(64 * WAVES,
-                                  DT == DT_F32X || (DT == DT_FP8 && WAVES == 4 && KSPLIT == 1 && MT <= 12 && LD == LD_F32) ? 2 : 1)
+                                  DT == DT_F32X ? 2 : 1)
 conv_igemm(ConvArgs a)
 {
     using Frag = typename Prec<DT>::Frag;
@@ -246,9 +116,6 @@ conv_igemm(ConvArgs a)
     // (GDN blocks of four unsplit waves keep idle waves: they take part in the
     // barriers of the shared weight and gamma staging)
     constexpr bool kGLds = KSPLIT == 1 && WAVES == 4 && (EP == EP_GDN || EP == EP_IGDN);
-    // (e4m3: 8 or 12 row blocks)
-    constexpr bool kALdsEarly = kGLds && DT != DT_F32X && LD != LD_RGB && MT % 4 == 0 &&
-                                (DT != DT_FP8 || (LD == LD_F32 && (MT == 8 || MT == 12)));
     // the split-FP32 form stages the (three times larger) weight tiles of its
     // GDN layers in LDS: a 2-stage ring filled from one register set (other
     // shapes would load them per wave)
@@ -257,7 +124,7 @@ conv_igemm(ConvArgs a)
     // one LDS buffer for the staged weight ring of the K loop and, after it,
     // the staged gamma slices of the GDN epilogue
     constexpr int kGP = (DT == DT_F32 || DT == DT_F32X) ? 3 : 2;   // bf16 parts of gamma
-    constexpr int kAWords = kALdsEarly ? (DT == DT_FP8 ? 2 * MT * 16 * 36 : 3 * MT * 16 * 20) : kALdsX ? 2 * MT * 16 * 52
+    constexpr int kAWords = kALdsX ? 2 * MT * 16 * 52
                           : LD == LD_TILE ? 2 * ((WAVES + 2) * (NT * 16 + 2) + 9 * MT * 16) * 16 : 0;
     constexpr int kGWords = kGLds ? 2 * kGP * MT * 16 * 16 : 0;
     constexpr int kSmemWords = (kAWords > kGWords ? kAWords : kGWords) > 0 ? (kAWords > kGWords ? kAWords : kGWords) : 4;
@@ -555,7 +422,7 @@ conv_igemm(ConvArgs a)
     constexpr int STAGE = (MT * (int)sizeof(Frag) + NT * (int)sizeof(BRaw)) / 4;   // VGPRs per chunk buffer
     constexpr int BUDGET = WAVES >= 8 ? 64 : 128;                     // VGPRs for the ring
     // (the image loader has only a handful of chunks: keep its ring short)
-    constexpr int P = DT == DT_F32X ? 2 : kALdsEarly ? 3
+    constexpr int P = DT == DT_F32X ? 2
                   : (LD == LD_RGB || BUDGET / STAGE < 2) ? 2 : (BUDGET / STAGE > 4 ? 4 : BUDGET / STAGE);
     const int K = DT == DT_FP8 ? (ntaps * CIN + KCH - 1) / KCH : ntaps * KC;
     const int nk = (K - kslot + KSPLIT - 1) / KSPLIT;
@@ -639,163 +506,6 @@ conv_igemm(ConvArgs a)
             loadB(kk / KC, kk % KC, B);
         }
     };
-    // Shared weights (GDN layers, one pixel tile per wave, no split-K): the
-    // four waves of a block need the same weight rows for every chunk, so the
-    // block stages each chunk's weight tile in LDS once (two 16-byte pieces
-    // per thread; e4m3: four) instead of every wave fetching it: a 3-stage
-    // LDS ring, filled two chunks ahead from registers loaded two chunks
-    // before that (e4m3: a 2-stage ring, below), one barrier per chunk.  The
-    // pixel operands keep their per-wave ring.
-    constexpr bool kALds = kALdsEarly;
-    if constexpr (kALds) {
-        static_assert(P == 3, "the shared-weight loop is written for a 3-deep ring");
-        // a chunk row is 64 bytes (FP32 / bf16) or 128 bytes (e4m3: the
-        // flattened (tap, channel) chunk, 32 bytes per lane group), padded by
-        // 16 bytes in LDS so the 16 rows of one fragment load hit distinct banks
-        constexpr int RB = KCH * (int)sizeof(WElem);
-        constexpr int PPR = RB / 16;                        // 16-byte pieces per row
-        constexpr int AROW = RB / 4 + 4;                    // LDS row pitch in dwords
-        constexpr int ROWS = MT * 16;
-        constexpr int NPIECE = ROWS * PPR / 256;            // pieces per thread per chunk
-        static_assert(ROWS * PPR % 256 == 0, "whole pieces per thread");
-        uint32_t* const As = smem;                          // [stages][ROWS][AROW]
-        static_assert((DT == DT_FP8 ? 2 : 3) * ROWS * AROW <= kSmemWords, "weight ring fits the LDS buffer");
-        const int tid = threadIdx.x;
-        int a_t = 0, a_kc = 0, a_k = 0;
-        auto a_gload = [&](u32x4 (&r)[NPIECE]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int i = 0; i < NPIECE; ++i) {
-                const int q = tid + i * 256, row = q / PPR, c16 = q - (q / PPR) * PPR;
-                const void* src;
-                if constexpr (DT == DT_FP8) {
-                    // flattened position of the piece; past the last tap: zeros
-                    const int f = a_k * KCH + c16 * 16, t = f / CIN, c = f - (f / CIN) * CIN;
-                    src = t < ntaps ? static_cast<const void*>(wbase + ((long)t * CoP + co0 + row) * CIN + c) : a.zero;
-                } else {
-                    src = wbase + ((long)a_t * CoP + co0 + row) * CIN + a_kc * KCH + c16 * (16 / (int)sizeof(WElem));
-                }
-                r[i] = *reinterpret_cast<const u32x4*>(src);
-            }
-            ++a_k;
-            if (++a_t == ntaps) {
-                a_t = 0;
-                ++a_kc;
-            }
-        };
-        auto a_store = [&](int stage, const u32x4 (&r)[NPIECE]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int i = 0; i < NPIECE; ++i) {
-                const int q = tid + i * 256, row = q / PPR, c16 = q - (q / PPR) * PPR;
-                *reinterpret_cast<u32x4*>(&As[(stage * ROWS + row) * AROW + c16 * 4]) = r[i];
-            }
-        };
-        auto a_frag = [&](int stage, Frag (&A)[MT]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const uint32_t* src = &As[(stage * ROWS + mt * 16 + l16) * AROW + kg * (RB / 16)];
-                if constexpr (DT == DT_FP8) {
-                    const u32x4 lo = *reinterpret_cast<const u32x4*>(src), hi = *reinterpret_cast<const u32x4*>(src + 4);
-                    A[mt] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-                } else {
-                    A[mt] = __builtin_bit_cast(Frag, *reinterpret_cast<const u32x4*>(src));
-                }
-            }
-        };
-        // pixels of chunk kk (the e4m3 loader takes the flat chunk index)
-        auto loadBs = [&](int kk, BRaw (&B)[NT]) __attribute__((always_inline)) {
-            if constexpr (DT == DT_FP8) loadB8(kk, B);
-            else cursor_loadB(B);
-        };
-      if constexpr (DT == DT_FP8) {
-        // e4m3: a two-stage ring, so that the kernel fits two waves per SIMD
-        // (the three-stage ring's register sets, with operands of 32 bytes
-        // per lane, need one wave per SIMD).  Chunk c sits in register set
-        // c % 2, LDS stage c % 2 and pixel buffer c % 2.  Step k issues the
-        // weight loads of chunk k + 2 (into the set of chunk k, stored one
-        // step earlier) and the pixel loads of chunk k + 1, multiplies chunk
-        // k, and stores chunk k + 1 (loaded at the start of step k - 1) into
-        // the stage chunk k - 1 used before the last barrier.
-        u32x4 ra[2][NPIECE];
-        BRaw Bp[2][NT];
-        if (0 < nk) a_gload(ra[0]);
-        if (1 < nk) a_gload(ra[1]);
-        if (0 < nk) loadBs(0, Bp[0]);
-        if (0 < nk) a_store(0, ra[0]);
-        __syncthreads();
-        auto step = [&](int k, auto jc, bool guard) __attribute__((always_inline)) {
-            constexpr int j = decltype(jc)::value;          // k % 2
-            if (!guard || k + 2 < nk) a_gload(ra[j]);
-            if (!guard || k + 1 < nk) loadBs(k + 1, Bp[1 - j]);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const uint32_t* src = &As[(j * ROWS + mt * 16 + l16) * AROW + kg * (RB / 16)];
-                const u32x4 lo = *reinterpret_cast<const u32x4*>(src), hi = *reinterpret_cast<const u32x4*>(src + 4);
-                const Frag A = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
-                                     (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                        A, Bp[j][nt], acc[mt][nt], 0, 0, 0, kE8M0One, 0, kE8M0One);
-            }
-            // (keeps the scheduler from sinking this chunk's products below
-            // the barrier, where they would hold two chunks of fragments)
-            __builtin_amdgcn_sched_barrier(0);
-            if (!guard || k + 1 < nk) a_store(1 - j, ra[1 - j]);
-            __syncthreads();
-        };
-        int k0 = 0;
-        using J0 = std::integral_constant<int, 0>;
-        using J1 = std::integral_constant<int, 1>;
-        for (; k0 + 3 < nk; k0 += 2) {
-            step(k0, J0{}, false);
-            step(k0 + 1, J1{}, false);
-        }
-        for (; k0 < nk; k0 += 2) {
-            step(k0, J0{}, true);
-            if (k0 + 1 < nk) step(k0 + 1, J1{}, true);
-        }
-      } else {
-        BRaw Bb[P][NT];
-        u32x4 ra[3][NPIECE];
-        // prologue: weights of chunks 0..2 in registers, 0 and 1 in LDS, 3 in flight
-        if (0 < nk) a_gload(ra[0]);
-        if (1 < nk) a_gload(ra[1]);
-        if (2 < nk) a_gload(ra[2]);
-#pragma unroll
-        for (int j = 0; j < P - 1; ++j)
-            if (j < nk) loadBs(j, Bb[j]);
-        if (0 < nk) a_store(0, ra[0]);
-        if (1 < nk) a_store(1, ra[1]);
-        if (3 < nk) a_gload(ra[0]);
-        __syncthreads();
-        // chunk k: weights in stage k % 3 (register set k % 3), pixels in Bb[k % 3]
-        // (j is a compile-time constant so that every ring index is static)
-        auto step = [&](int k, auto jc, bool guard) __attribute__((always_inline)) {
-            constexpr int j = decltype(jc)::value;
-            if (!guard || k + P - 1 < nk) loadBs(k + P - 1, Bb[(j + P - 1) % P]);
-            Frag A[MT];
-            a_frag(j, A);
-            compute(A, Bb[j]);
-            if (!guard || k + 2 < nk) a_store((j + 2) % 3, ra[(j + 2) % 3]);
-            if (!guard || k + 4 < nk) a_gload(ra[(j + 1) % 3]);
-            __syncthreads();
-        };
-        int k0 = 0;
-        using J0 = std::integral_constant<int, 0>;
-        using J1 = std::integral_constant<int, 1>;
-        using J2 = std::integral_constant<int, 2>;
-        for (; k0 + 6 < nk; k0 += 3) {
-            step(k0, J0{}, false);
-            step(k0 + 1, J1{}, false);
-            step(k0 + 2, J2{}, false);
-        }
-        for (; k0 < nk; k0 += 3) {
-            step(k0, J0{}, true);
-            if (k0 + 1 < nk) step(k0 + 1, J1{}, true);
-            if (k0 + 2 < nk) step(k0 + 2, J2{}, true);
-        }
-      }
-    }
     if constexpr (kALdsX) {
         // Split-FP32 weights: per chunk a row holds 32 channels x 3 parts
         // (192 bytes, twelve 16-byte pieces), padded to 208 bytes in LDS so
@@ -1002,9 +712,9 @@ conv_igemm(ConvArgs a)
             }
         }
     }
-    Frag Ab[(kALds || kALdsX || kTile) ? 1 : P][MT];
-    BRaw Bb[(kALds || kALdsX || kTile) ? 1 : P][NT];
-    if constexpr (!kALds && !kALdsX && !kTile) {
+    Frag Ab[(kALdsX || kTile) ? 1 : P][MT];
+    BRaw Bb[(kALdsX || kTile) ? 1 : P][NT];
+    if constexpr (!kALdsX && !kTile) {
     // steady state: every step issues its prefetch unconditionally, so the
     // wait before a chunk's MFMAs only covers that chunk's own loads.  The
     // prologue before it is unconditional too: a load that some path skips
@@ -1419,26 +1129,23 @@ struct KernelEntry {
 #define LIC_K(TAG, CIN, MT, NT, WV, LD, EP) LIC_KS(TAG, CIN, MT, NT, WV, 1, LD, EP)
 // bf16 operand variants of the analysis / synthesis layers
 #define LIC_KB(TAG, CIN, MT, NT, WV, LD, EP) LIC_KSD(TAG, CIN, MT, NT, WV, 1, LD, EP, DT_BF16)
-#define LIC_KGB(TAG, CIN, MT, NT, LD, EP) \
-    LIC_KSD(TAG, CIN, MT, NT, 4, 1, LD, EP, DT_BF16), LIC_KSD(TAG, CIN, MT, NT, 4, 4, LD, EP, DT_BF16)
+#define LIC_KGB(TAG, CIN, MT, NT, LD, EP) LIC_KSD(TAG, CIN, MT, NT, 4, 4, LD, EP, DT_BF16)
 #define LIC_K2B(TAG, CIN, LD, EP)                                                                \
     LIC_KSD(TAG, CIN, 4, 2, 4, 1, LD, EP, DT_BF16), LIC_KSD(TAG, CIN, 4, 2, 4, 4, LD, EP, DT_BF16), \
         LIC_KSD(TAG, CIN, 4, 2, 8, 8, LD, EP, DT_BF16), LIC_KSD(TAG, CIN, 1, 1, 8, 8, LD, EP, DT_BF16)
 // split-FP32 operands: whole-frame GDN layers of the FP32 form
 #define LIC_KX(TAG, CIN, MT, NT, LD, EP) LIC_KSD(TAG, CIN, MT, NT, 4, 1, LD, EP, DT_F32X)
 // e4m3 operand variants (precision form): g_a and g_s
-#define LIC_KF(TAG, CIN, MT, NT, WV, LD, EP) LIC_KSD(TAG, CIN, MT, NT, WV, 1, LD, EP, DT_FP8)
-#define LIC_KGF(TAG, CIN, MT, NT, LD, EP) \
-    LIC_KSD(TAG, CIN, MT, NT, 4, 1, LD, EP, DT_FP8), LIC_KSD(TAG, CIN, MT, NT, 4, 4, LD, EP, DT_FP8)
+#define LIC_KGF(TAG, CIN, MT, NT, LD, EP) LIC_KSD(TAG, CIN, MT, NT, 4, 4, LD, EP, DT_FP8)
 #define LIC_K2F(TAG, CIN, LD, EP)                                                              \
     LIC_KSD(TAG, CIN, 4, 2, 4, 1, LD, EP, DT_FP8), LIC_KSD(TAG, CIN, 4, 2, 4, 4, LD, EP, DT_FP8), \
         LIC_KSD(TAG, CIN, 4, 2, 8, 8, LD, EP, DT_FP8), LIC_KSD(TAG, CIN, 1, 1, 8, 8, LD, EP, DT_FP8)
 // the tile configurations of a non-GDN layer: large (4 m-tiles x 2 n-tiles,
 // 4 pixel-parallel waves), large with 4-way split-K, and small (1 x 1) with
 // 8-way split-K, for grids too small to fill the chip
-// GDN / IGDN layers: pixel-parallel, or 4-way split-K with the
-// normalisation done by the first wave after the reduction
-#define LIC_KG(TAG, CIN, MT, NT, LD, EP) LIC_K(TAG, CIN, MT, NT, 4, LD, EP), LIC_KS(TAG, CIN, MT, NT, 4, 4, LD, EP)
+// GDN / IGDN layers of small grids: 4-way split-K with the normalisation done
+// by the first wave after the reduction (whole frames: gdn_kernels.hip)
+#define LIC_KG(TAG, CIN, MT, NT, LD, EP) LIC_KS(TAG, CIN, MT, NT, 4, 4, LD, EP)
 #define LIC_K2(TAG, CIN, LD, EP)                                                               \
     LIC_K(TAG, CIN, 4, 2, 4, LD, EP), LIC_KS(TAG, CIN, 4, 2, 4, 4, LD, EP), LIC_KS(TAG, CIN, 4, 2, 8, 8, LD, EP), \
         LIC_KS(TAG, CIN, 1, 1, 8, 8, LD, EP)
@@ -1466,25 +1173,14 @@ static const KernelEntry kEntries[] = {
     LIC_K2(LIC_EP2A, 512, LD_F32, EP_MSCALE),
     LIC_K2(LIC_EP0N, 768, LD_F32, EP_RELU), LIC_K2(LIC_EP1N, 640, LD_F32, EP_RELU),
     LIC_K2(LIC_EP2N, 512, LD_F32, EP_MSCALE),
-    LIC_KG(LIC_GS0, 192, 8, 2, LD_F32, EP_IGDN), LIC_KX(LIC_GS0, 192, 8, 2, LD_F32, EP_IGDN),
-    LIC_KX(LIC_GS0, 192, 8, 1, LD_F32, EP_IGDN), LIC_KGB(LIC_GS0, 192, 8, 2, LD_F32, EP_IGDN),
-    LIC_KB(LIC_GS0, 192, 8, 1, 4, LD_F32, EP_IGDN),
+    LIC_KG(LIC_GS0, 192, 8, 2, LD_F32, EP_IGDN), LIC_KGB(LIC_GS0, 192, 8, 2, LD_F32, EP_IGDN),
     // g_s
     LIC_KG(LIC_GS0, 192, 8, 2, LD_I8, EP_IGDN), LIC_KG(LIC_GS0, 320, 12, 1, LD_I8, EP_IGDN),
     LIC_KG(LIC_GS1, 128, 8, 2, LD_F32, EP_IGDN), LIC_KG(LIC_GS1, 192, 12, 1, LD_F32, EP_IGDN),
     LIC_KG(LIC_GS2, 128, 8, 2, LD_F32, EP_IGDN), LIC_KG(LIC_GS2, 192, 12, 1, LD_F32, EP_IGDN),
     LIC_K(LIC_GS3, 128, 1, 4, 4, LD_F32, EP_RGB), LIC_K(LIC_GS3, 192, 1, 4, 4, LD_F32, EP_RGB),
     LIC_K(LIC_GS3, 128, 1, 4, 4, LD_TILE, EP_RGB), LIC_K(LIC_GS3, 192, 1, 4, 4, LD_TILE, EP_RGB),
-    LIC_KX(LIC_GA1, 128, 8, 2, LD_F32, EP_GDN), LIC_KX(LIC_GA1, 192, 12, 1, LD_F32, EP_GDN),
-    LIC_KX(LIC_GA2, 128, 8, 2, LD_F32, EP_GDN), LIC_KX(LIC_GA2, 192, 12, 1, LD_F32, EP_GDN),
-    LIC_KX(LIC_GS0, 192, 8, 2, LD_I8, EP_IGDN), LIC_KX(LIC_GS0, 320, 12, 1, LD_I8, EP_IGDN),
-    LIC_KX(LIC_GS1, 128, 8, 2, LD_F32, EP_IGDN), LIC_KX(LIC_GS1, 192, 12, 1, LD_F32, EP_IGDN),
-    LIC_KX(LIC_GS2, 128, 8, 2, LD_F32, EP_IGDN), LIC_KX(LIC_GS2, 192, 12, 1, LD_F32, EP_IGDN),
     LIC_KX(LIC_GA0, 96, 8, 2, LD_RGB, EP_GDN), LIC_KX(LIC_GA0, 96, 12, 1, LD_RGB, EP_GDN),
-    // (one pixel group per wave: grids between half and one wave per SIMD)
-    LIC_KX(LIC_GA1, 128, 8, 1, LD_F32, EP_GDN), LIC_KX(LIC_GA2, 128, 8, 1, LD_F32, EP_GDN),
-    LIC_KX(LIC_GS0, 192, 8, 1, LD_I8, EP_IGDN), LIC_KX(LIC_GS1, 128, 8, 1, LD_F32, EP_IGDN),
-    LIC_KX(LIC_GS2, 128, 8, 1, LD_F32, EP_IGDN),
     // bf16 operands (precision form): g_a and g_s; h_a / h_s stay FP32
     LIC_KB(LIC_GA0, 96, 8, 2, 4, LD_RGB, EP_GDN), LIC_KB(LIC_GA0, 96, 12, 1, 4, LD_RGB, EP_GDN),
     LIC_KGB(LIC_GA1, 128, 8, 2, LD_F32, EP_GDN), LIC_KGB(LIC_GA1, 192, 12, 1, LD_F32, EP_GDN),
@@ -1495,14 +1191,9 @@ static const KernelEntry kEntries[] = {
     LIC_KGB(LIC_GS2, 128, 8, 2, LD_F32, EP_IGDN), LIC_KGB(LIC_GS2, 192, 12, 1, LD_F32, EP_IGDN),
     LIC_KB(LIC_GS3, 128, 1, 4, 4, LD_F32, EP_RGB), LIC_KB(LIC_GS3, 192, 1, 4, 4, LD_F32, EP_RGB),
     LIC_KB(LIC_GS3, 128, 1, 4, 4, LD_TILE, EP_RGB), LIC_KB(LIC_GS3, 192, 1, 4, 4, LD_TILE, EP_RGB),
-    LIC_KB(LIC_GA1, 128, 8, 1, 4, LD_F32, EP_GDN), LIC_KB(LIC_GA2, 128, 8, 1, 4, LD_F32, EP_GDN),
-    LIC_KB(LIC_GS0, 192, 8, 1, 4, LD_I8, EP_IGDN), LIC_KB(LIC_GS1, 128, 8, 1, 4, LD_F32, EP_IGDN),
-    LIC_KB(LIC_GS2, 128, 8, 1, 4, LD_F32, EP_IGDN),
     // e4m3 operands (precision form): g_a and g_s
     LIC_KGF(LIC_GA1, 128, 8, 2, LD_F32, EP_GDN), LIC_KGF(LIC_GA1, 192, 12, 1, LD_F32, EP_GDN),
     LIC_KGF(LIC_GA2, 128, 8, 2, LD_F32, EP_GDN), LIC_KGF(LIC_GA2, 192, 12, 1, LD_F32, EP_GDN),
-    // one 16-pixel group per wave (grids between half and one wave per SIMD)
-    LIC_KF(LIC_GA2, 128, 8, 1, 4, LD_F32, EP_GDN),
     LIC_K2F(LIC_GA3, 128, LD_F32, EP_QUANT), LIC_K2F(LIC_GA3, 192, LD_F32, EP_QUANT),
     // (g_s's first layer runs on bf16 operands in this form: no e4m3 kernel)
     LIC_KGF(LIC_GS1, 128, 8, 2, LD_F32, EP_IGDN), LIC_KGF(LIC_GS1, 192, 12, 1, LD_F32, EP_IGDN),

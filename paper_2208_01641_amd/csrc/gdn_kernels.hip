@@ -1,0 +1,545 @@
+// GDN / IGDN convolution layers of whole frames on MFMA (gfx950): the
+// implicit GEMM of conv_kernels.hip with both operands staged in LDS.
+//
+// What bounds the direct form: the MFMA operand layout puts 16 pixels in 16
+// neighbouring lanes, so a gather straight into registers sends 64 lanes to
+// 64 separate 16-byte pieces, and the vector memory path takes one piece a
+// clock (measured 15.8 bytes a clock and CU, against 61 when the four lanes
+// of a quad read one 64-byte run).  Here every global load is such a run:
+//   * weights are packed in fragment order (lane by lane, 1 KB per fragment),
+//     so a chunk's weight tile goes from memory to LDS linearly and is read
+//     back linearly (LDS reads at 220 bytes a clock; 64-byte rows padded to 80
+//     bytes gave 124);
+//   * a wave loads its pixels' channel runs with consecutive lanes on one
+//     pixel; the 16-byte pieces of a row are stored rotated by the pixel
+//     index (an exclusive or), which makes the fragment reads conflict-free
+//     (a b128 read takes lanes 0-7 with 16-23, 8-15 with 24-31, ... together);
+//   * gamma comes in fragment order too, and the outputs are transposed in LDS
+//     so that each pixel's channels leave in whole 16-byte pieces.
+// All of it goes straight from memory to LDS (global_load_lds_dwordx4) into a
+// ring of ST stages, ST - 1 chunks ahead, with one barrier per chunk and a
+// wait that leaves the later chunks in flight.
+//
+// The products, their order and the order of the channels and taps are those
+// of conv_igemm, so the results are the same bits.
+//
+// Measured against the direct form (kernel time, us): 720p split-FP32 GA1
+// 289 -> 252, GS2 382 -> 333; bf16 GA1 89 -> 68, GS2 129 -> 104; e4m3 GA1 50 ->
+// 40, GS2 90 -> 72; four 1080p frames at 192 channels bf16 GA1 1838 -> 1005,
+// GS2 2780 -> 1428, e4m3 GA1 1041 -> 608, GS2 1917 -> 988.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "../../include/lic.h"
+#include "conv_args.h"
+#include "kernels.h"
+#include "mfma_common.h"
+
+namespace lic {
+
+// s_waitcnt vmcnt(N) alone (expcnt and lgkmcnt at their maxima)
+template <int N> __device__ __forceinline__ void wait_vm()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+// workgroup barrier that orders LDS accesses only: loads into LDS that are
+// still in flight are waited for by wait_vm where their stage is used
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// orders one wave's LDS accesses before and after (lanes read each other's)
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// WAVES: 4 with two blocks per CU, or 8 with one where two blocks' stages do
+// not fit its 160 KB of LDS (either way two waves per SIMD, 256 registers).
+template <int TAG, int CIN, int MT, int NT, int WAVES, int ST, int LD, int EP, int DT>
+__global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(ConvArgs a)
+{
+    using Elem = typename std::conditional<LD == LD_I8, int8_t, typename Prec<DT>::Elem>::type;
+    static_assert(DT == DT_F32X || DT == DT_BF16 || DT == DT_FP8, "matrix-core forms");
+    static_assert(LD == LD_F32 || (LD == LD_I8 && DT != DT_FP8), "NHWC activations or symbols");
+    constexpr int KCH = Prec<DT>::KCH;
+    constexpr int SUB = DT == DT_F32X ? 3 : DT == DT_FP8 ? 2 : 1;  // 1 KB weight fragments per 16 rows and chunk
+    constexpr int ESZ = (int)sizeof(Elem);
+    constexpr int RB = KCH * ESZ;                                  // bytes of a pixel and chunk
+    constexpr int LPR = RB / 16;                                   // lanes (16-byte pieces) per pixel
+    constexpr int PPI = 64 / LPR;                                  // pixels per load instruction
+    constexpr int NB = (NT * 16 + PPI - 1) / PPI;                  // pixel loads per wave and chunk
+    constexpr int AP = MT * SUB;                                   // weight fragments (KB) per chunk
+    constexpr int AW = (AP + WAVES - 1) / WAVES;                   // loads of them per wave (past the end: the last again)
+    constexpr int L = AW + NB;                                     // loads per wave and chunk
+    static_assert(RB == 32 || RB == 64 || RB == 128, "whole pieces per pixel");
+    constexpr int STW = (AP + WAVES * NB) * 256;                   // words per stage
+    constexpr int GP = DT == DT_F32X ? 3 : 2;                      // bf16 parts of gamma and x*x
+    constexpr int NPAIR = MT / 2;
+    constexpr int GSW = MT * GP * 256;                             // words per 32-channel gamma slice
+    constexpr int OROWMAX = MT * 16 + 4;                           // words per staged output pixel (float)
+    constexpr int OUTW = WAVES * 16 * (DT == DT_F32X ? OROWMAX : MT * 8 + 4);
+    constexpr int MUW = LD == LD_I8 ? CIN : 0;                     // the symbols' offsets, behind the stages
+    constexpr int SMW = ST * STW + MUW > OUTW ? ST * STW + MUW : OUTW;
+    static_assert(SMW * 4 <= (WAVES == 4 ? 81920 : 163840), "two waves per SIMD");
+    constexpr int GSL = SMW / GSW < NPAIR ? SMW / GSW : NPAIR;     // gamma slices in LDS at once
+    static_assert(GSL >= 2, "gamma ring");
+    constexpr int GW = (MT * GP + WAVES - 1) / WAVES;              // loads of a slice per wave
+    __shared__ __attribute__((aligned(16))) uint32_t smem[SMW];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, kg = lane >> 4;
+    int logical = xcd_logical_tile(blockIdx.x, gridDim.x);
+    const int phase = logical % a.nphase;
+    const int tile = logical / a.nphase;
+    const PhaseDesc* __restrict__ ph = a.ph + phase;
+    const int ntaps = ph->ntaps;
+    // lane t keeps the offsets of tap t
+    const int tapv = lane < ntaps ? (((int)ph->dy[lane] & 0xffff) | ((int)ph->dx[lane] << 16)) : 0;
+    const uint8_t* __restrict__ wt = static_cast<const uint8_t*>(a.wt) + ph->wtoff;
+    const int HWg = a.Hg * a.Wg;
+    const int total = a.n * HWg;
+    const int pix0 = (tile * WAVES + wave) * (NT * 16);
+
+    // loader: this lane's pixel and piece in each of the NB loads of a chunk.
+    // A pixel past the end gets an origin no tap brings into the image.
+    const int lpx = lane / LPR, slot = lane % LPR;
+    auto rot = [](int p) { return LPR == 2 ? 0 : LPR == 4 ? (p >> 1) & 3 : ((p >> 1) & 1) | (((p >> 2) & 1) << 2); };
+    int oy0[NB], ox0[NB], pc[NB];
+    const uint8_t* pb[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int pl = i * PPI + lpx;
+        const int p = pl < NT * 16 ? pix0 + pl : total;
+        const int q = p < total ? p : 0;
+        const int im = q / HWg, r = q - im * HWg;
+        const int y = r / a.Wg, x = r - y * a.Wg;
+        oy0[i] = p < total ? y * a.s_in : -(1 << 20);
+        ox0[i] = x * a.s_in;
+        pc[i] = (slot ^ rot(pl & 15)) * 16;
+        pb[i] = static_cast<const uint8_t*>(a.in) +
+                (((long)im * a.Hin + y * a.s_in) * a.Win + x * a.s_in) * (long)(CIN * ESZ) + (DT == DT_FP8 ? 0 : pc[i]);
+    }
+
+    constexpr int KC = DT == DT_FP8 ? 1 : CIN / KCH;
+    const int nk = DT == DT_FP8 ? (ntaps * CIN + KCH - 1) / KCH : ntaps * KC;
+    int i_t = 0, i_s = 0, i_k = 0, i_st = 0;             // next chunk to load: tap, channel slice, index, stage
+    auto tap = [&](int t, int& dy, int& dx) __attribute__((always_inline)) {
+        const int tv = __builtin_amdgcn_readlane(tapv, t < ntaps ? t : 0);
+        dy = t < ntaps ? (int)(short)(tv & 0xffff) : -(1 << 20);
+        dx = tv >> 16;
+    };
+    auto issue = [&]() __attribute__((always_inline)) {
+        uint32_t* const st = smem + i_st * STW;
+        const uint8_t* ag = wt + (size_t)i_k * (AP * 1024);
+#pragma unroll
+        for (int u = 0; u < AW; ++u) {
+            const int f = AP % WAVES == 0 ? wave * AW + u : min(wave * AW + u, AP - 1);
+#if defined(__HIP_DEVICE_COMPILE__)
+            __builtin_amdgcn_global_load_lds(ag + f * 1024 + lane * 16, st + f * 256, 16, 0, 0);
+#endif
+            (void)f;
+        }
+        int dyA, dxA, dyB = 0, dxB = 0;
+        long offA, offB = 0;
+        int c0 = 0;
+        if constexpr (DT == DT_FP8) {
+            const int f0 = i_k * KCH, tA = f0 / CIN;
+            c0 = f0 - tA * CIN;
+            tap(tA, dyA, dxA);
+            offA = ((long)dyA * a.Win + dxA) * CIN + c0;
+            if constexpr (CIN % KCH != 0) {
+                tap(tA + 1, dyB, dxB);
+                offB = ((long)dyB * a.Win + dxB) * CIN + c0 - CIN;
+            }
+        } else {
+            tap(i_t, dyA, dxA);
+            offA = (((long)dyA * a.Win + dxA) * CIN + i_s * KCH) * ESZ;
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            int dy = dyA, dx = dxA;
+            const uint8_t* src = pb[i] + offA;
+            if constexpr (DT == DT_FP8) {
+                if constexpr (CIN % KCH != 0) {
+                    const bool second = c0 + pc[i] >= CIN;
+                    dy = second ? dyB : dyA;
+                    dx = second ? dxB : dxA;
+                    src = pb[i] + (second ? offB : offA);
+                }
+                src += pc[i];
+            }
+            const bool ok = ((unsigned)(oy0[i] + dy) < (unsigned)a.Hin) & ((unsigned)(ox0[i] + dx) < (unsigned)a.Win);
+            src = ok ? src : static_cast<const uint8_t*>(a.zero);
+#if defined(__HIP_DEVICE_COMPILE__)
+            __builtin_amdgcn_global_load_lds(src, st + (AP + wave * NB + i) * 256, 16, 0, 0);
+#endif
+            (void)src;
+        }
+        (void)ag;
+        (void)st;
+        if (++i_t == ntaps) {
+            i_t = 0;
+            ++i_s;
+        }
+        ++i_k;
+        if (++i_st == ST) i_st = 0;
+    };
+
+    // symbols: the offsets in LDS, and the pixels of this lane's fragments
+    // (an out-of-image tap reads symbol 0 and must not add the offset)
+    float* const mus = reinterpret_cast<float*>(smem + ST * STW);
+    int fy[NT], fx[NT], c_t = 0, c_s = 0;
+    if constexpr (LD == LD_I8) {
+        for (int c = threadIdx.x; c < CIN; c += 64 * WAVES) mus[c] = a.mu_in[c];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int p = pix0 + nt * 16 + l16;
+            const int q = p < total ? p : 0;
+            const int r = q - (q / HWg) * HWg;
+            fy[nt] = p < total ? (r / a.Wg) * a.s_in : -(1 << 20);
+            fx[nt] = (r - (r / a.Wg) * a.Wg) * a.s_in;
+        }
+    }
+
+    f4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        f4 b = {0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (DT != DT_FP8) b = *reinterpret_cast<const f4*>(a.bias + mt * 16 + kg * 4);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = b;
+    }
+
+    // One chunk: the fragments of stage st are read first (LDS returns them in
+    // order, so the products start on the first while the rest arrive), the
+    // loads of a later chunk are issued in their shadow, then the products.
+    // Split-FP32 holds two of its three-part weight fragments at a time.
+    const int brow = LPR == 2 ? l16 * 8 + kg * 2 : l16 * (RB / 4) + (((LPR == 4 ? kg : 2 * kg) ^ rot(l16)) * 4);
+    constexpr int PF = DT == DT_F32X ? 2 : MT;
+    auto step = [&](const uint32_t* st, auto more) __attribute__((always_inline)) {
+        const uint32_t* bs = st + (AP + wave * NB) * 256 + brow;
+        const uint32_t* bs2 = st + (AP + wave * NB) * 256 + (brow ^ 4);
+        const uint32_t* as = st + lane * 4;
+        u32x4 Bl[NT], Bh[NT], A[MT][SUB];
+        uint2 Bs[NT];
+        f4 mu[2];
+        if constexpr (LD == LD_I8) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) Bs[nt] = *reinterpret_cast<const uint2*>(bs + nt * 16 * (RB / 4));
+#pragma unroll
+            for (int e = 0; e < 2; ++e) mu[e] = *reinterpret_cast<const f4*>(mus + c_s * KCH + kg * 8 + e * 4);
+        } else
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            Bl[nt] = *reinterpret_cast<const u32x4*>(bs + nt * 16 * (RB / 4));
+            if constexpr (LPR == 8) Bh[nt] = *reinterpret_cast<const u32x4*>(bs2 + nt * 16 * (RB / 4));
+        }
+        auto readA = [&](int mt) __attribute__((always_inline)) {
+#pragma unroll
+            for (int g = 0; g < SUB; ++g) A[mt][g] = *reinterpret_cast<const u32x4*>(as + (mt * SUB + g) * 256);
+        };
+#pragma unroll
+        for (int mt = 0; mt < PF; ++mt) readA(mt);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(more)::value) issue();
+        Split3 Bx[NT];
+        if constexpr (LD == LD_I8) {
+            int dy, dx;
+            tap(c_t, dy, dx);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const bool ok = ((unsigned)(fy[nt] + dy) < (unsigned)a.Hin) & ((unsigned)(fx[nt] + dx) < (unsigned)a.Win);
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    v[e] = (float)(int8_t)((e < 4 ? Bs[nt].x : Bs[nt].y) >> (8 * (e % 4))) + (ok ? mu[e / 4][e % 4] : 0.0f);
+                if constexpr (DT == DT_F32X) {
+                    Bx[nt] = split3(v);
+                } else {
+                    bf16x8 h;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) h[e] = (__bf16)v[e];
+                    Bl[nt] = __builtin_bit_cast(u32x4, h);
+                }
+            }
+            if (++c_t == ntaps) {
+                c_t = 0;
+                ++c_s;
+            }
+        } else if constexpr (DT == DT_F32X) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const f4 lo = __builtin_bit_cast(f4, Bl[nt]), hi = __builtin_bit_cast(f4, Bh[nt]);
+                const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                Bx[nt] = split3(v);
+            }
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            if constexpr (DT == DT_F32X) {
+                // the six part products, smallest first
+                constexpr int pa[6] = {0, 1, 2, 0, 1, 0}, pbx[6] = {2, 1, 0, 1, 0, 0};
+#pragma unroll
+                for (int s = 0; s < 6; ++s)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[mt][pa[s]]),
+                                                                              Bx[nt].p[pbx[s]], acc[mt][nt], 0, 0, 0);
+                if (mt + PF < MT) readA(mt + PF);
+                __builtin_amdgcn_sched_barrier(0);
+            } else if constexpr (DT == DT_BF16) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[mt][0]),
+                                                                          __builtin_bit_cast(bf16x8, Bl[nt]), acc[mt][nt], 0, 0, 0);
+            } else {
+                auto cat = [](const u32x4& lo, const u32x4& hi) {
+                    return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+                };
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    acc[mt][nt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                        cat(A[mt][0], A[mt][1]), cat(Bl[nt], Bh[nt]), acc[mt][nt], 0, 0, 0, kE8M0One, 0, kE8M0One);
+            }
+        }
+    };
+
+    // chunks 0 .. ST - 2 in flight; step k waits for chunk k, lets every
+    // wave finish chunk k - 1 (whose stage chunk k + ST - 1 then takes)
+#pragma unroll
+    for (int j = 0; j < ST - 1; ++j)
+        if (j < nk) issue();
+    int c_st = 0, k = 0;
+    for (; k + ST - 1 < nk; ++k) {
+        wait_vm<(ST - 2) * L>();
+        lds_barrier();
+        step(smem + c_st * STW, std::true_type{});
+        if (++c_st == ST) c_st = 0;
+    }
+    for (; k < nk; ++k) {
+        wait_vm<0>();
+        lds_barrier();
+        step(smem + c_st * STW, std::false_type{});
+        if (++c_st == ST) c_st = 0;
+    }
+    lds_barrier();                                      // every stage is free
+
+    // ------------------------------------------------------------ GDN
+    // n = beta + gamma (x*x) as in conv_igemm: x*x and gamma in GP bf16 parts,
+    // 32 channels per K chunk; gamma slice p = [mt][part][lane][8]
+    const uint8_t* gt = static_cast<const uint8_t*>(a.gt);
+    auto g_issue = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < GW; ++u) {
+            const int f = MT * GP % WAVES == 0 ? wave * GW + u : min(wave * GW + u, MT * GP - 1);
+#if defined(__HIP_DEVICE_COMPILE__)
+            __builtin_amdgcn_global_load_lds(gt + ((size_t)p * (MT * GP) + f) * 1024 + lane * 16,
+                                             smem + (p % GSL) * GSW + f * 256, 16, 0, 0);
+#endif
+            (void)f;
+        }
+    };
+    if constexpr (DT == DT_FP8) {
+        // undo the operand scales, then add the bias
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const f4 rs = *reinterpret_cast<const f4*>(a.rscale + mt * 16 + kg * 4);
+            const f4 b = *reinterpret_cast<const f4*>(a.bias + mt * 16 + kg * 4);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = acc[mt][nt] * rs + b;
+        }
+    }
+    f4 nacc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const f4 b = *reinterpret_cast<const f4*>(a.beta + mt * 16 + kg * 4);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) nacc[mt][nt] = b;
+    }
+#pragma unroll
+    for (int p = 0; p < GSL; ++p) g_issue(p);
+    auto pair = [&](auto pc_) __attribute__((always_inline)) {
+        constexpr int p = decltype(pc_)::value;
+        bf16x8 S[GP][NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            float r[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float x = acc[2 * p + i / 4][nt][i % 4];
+                r[i] = a.norm1 ? fabsf(x) : x * x;
+            }
+            bf16x8 parts[GP];
+            split_parts<GP>(r, parts);
+#pragma unroll
+            for (int g = 0; g < GP; ++g) S[g][nt] = parts[g];
+        }
+        // slices issued so far: GSL at first, then one more per step from step 1 on
+        constexpr int issued = p == 0 ? GSL : (GSL + p - 1 < NPAIR ? GSL + p - 1 : NPAIR);
+        wait_vm<(issued - 1 - p) * GW>();
+        lds_barrier();
+        if constexpr (p >= 1 && p - 1 + GSL < NPAIR) g_issue(p - 1 + GSL);
+        const uint32_t* gs = smem + (p % GSL) * GSW + lane * 4;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            bf16x8 G[GP];
+#pragma unroll
+            for (int g = 0; g < GP; ++g)
+                G[g] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(gs + (mt * GP + g) * 256));
+            auto mul = [&](int g, int s) __attribute__((always_inline)) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    nacc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(G[g], S[s][nt], nacc[mt][nt], 0, 0, 0);
+            };
+            if constexpr (GP == 3) {
+                mul(0, 2);
+                mul(1, 1);
+                mul(2, 0);
+            }
+            mul(0, 1);
+            mul(1, 0);
+            mul(0, 0);
+        }
+    };
+    [&]<int... P>(std::integer_sequence<int, P...>) __attribute__((always_inline)) {
+        (pair(std::integral_constant<int, P>{}), ...);
+    }(std::make_integer_sequence<int, NPAIR>{});
+    lds_barrier();                                      // the last slice has been read
+
+    // ------------------------------------------------------------ output
+    // y = x / sqrt(n) (inverse: x sqrt(n)); 1DN: x / n (x n).  Each wave
+    // writes its pixels' channels to LDS rows and then to memory in 16-byte
+    // pieces, consecutive lanes on one pixel; the 16 bytes of padding per row
+    // (which spread the rows over the banks) hold the pixel's output offset.
+    auto emit = [&](auto oec) __attribute__((always_inline)) {
+        constexpr int OE = decltype(oec)::value;        // bytes per stored value
+        constexpr int OROW = MT * 16 * OE / 4 + 4;      // words per row
+        uint32_t* const ob = smem + wave * (16 * OROW);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int p = pix0 + nt * 16 + l16;
+            const bool pv = p < total;
+            const int q = pv ? p : 0;
+            const int im = q / HWg, r = q - im * HWg;
+            const int y = r / a.Wg, x = r - y * a.Wg;
+            uint32_t* const row = ob + l16 * OROW;
+            if (kg == 0) {
+                const long o = pv ? (((long)im * a.Hout + y * a.s_out + ph->oy) * a.Wout + x * a.s_out + ph->ox) *
+                                        (a.co_ld ? a.co_ld : a.Co) + a.co_off
+                                  : -1L;
+                *reinterpret_cast<long*>(row + MT * 16 * OE / 4) = o;
+            }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                f4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float nv = nacc[mt][nt][i];
+                    if (EP == EP_GDN)
+                        v[i] = acc[mt][nt][i] * (a.norm1 ? __builtin_amdgcn_rcpf(nv) : __builtin_amdgcn_rsqf(nv));
+                    else
+                        v[i] = acc[mt][nt][i] * (a.norm1 ? nv : __builtin_amdgcn_sqrtf(nv));
+                }
+                if constexpr (OE == 4) {
+                    *reinterpret_cast<f4*>(row + mt * 16 + kg * 4) = v;
+                } else if constexpr (OE == 2) {
+                    bf16x4 h;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) h[i] = (__bf16)v[i];
+                    *reinterpret_cast<bf16x4*>(row + mt * 8 + kg * 2) = h;
+                } else {
+                    const f4 w = a.out_q * v;
+                    if (a.sat) {
+                        const bool s = pv && (fabsf(w[0]) > 448.0f || fabsf(w[1]) > 448.0f || fabsf(w[2]) > 448.0f ||
+                                              fabsf(w[3]) > 448.0f);
+                        const unsigned long long m = __ballot(s);
+                        if (m && lane == __ffsll((long long)m) - 1) atomicAdd(a.sat, (unsigned long long)__popcll(m));
+                    }
+                    row[mt * 4 + kg] = e4m3x2(w[0], w[1]) | (e4m3x2(w[2], w[3]) << 16);
+                }
+            }
+            wave_order();
+            constexpr int PPR = MT * OE;                // 16-byte pieces per pixel
+            static_assert(16 * PPR % 64 == 0, "whole stores");
+#pragma unroll
+            for (int j = 0; j < 16 * PPR / 64; ++j) {
+                const int q2 = j * 64 + lane, p2 = q2 / PPR, c = q2 - (q2 / PPR) * PPR;
+                const uint32_t* orow = ob + p2 * OROW;
+                const long o = *reinterpret_cast<const long*>(orow + MT * 16 * OE / 4);
+                const u32x4 v = *reinterpret_cast<const u32x4*>(orow + c * 4);
+                if (o >= 0) *reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.out) + o * OE + c * 16) = v;
+            }
+            wave_order();
+        }
+    };
+    if constexpr (DT == DT_F32X) {
+        emit(std::integral_constant<int, 4>{});
+    } else if constexpr (DT == DT_BF16) {
+        if (a.out_e4m3) emit(std::integral_constant<int, 1>{});
+        else emit(std::integral_constant<int, 2>{});
+    } else {
+        if (a.out_bf16) emit(std::integral_constant<int, 2>{});
+        else emit(std::integral_constant<int, 1>{});
+    }
+}
+
+// ---------------------------------------------------------------- registry
+struct GdnEntry {
+    KernelKey key;
+    void (*fn)(ConvArgs);
+};
+
+#define LIC_G(TAG, CIN, MT, NT, WV, ST, LD, EP, DT) \
+    {{TAG, CIN, MT, NT, WV, 1, LD, EP, DT}, gdn_staged<TAG, CIN, MT, NT, WV, ST, LD, EP, DT>}
+// one layer at 128 and 192 channels; NT = 1 for grids that would leave SIMDs
+// idle with two 16-pixel tiles per wave (its stages are smaller: more of them)
+#define LIC_GX(TAG, EP)                                                                                        \
+    LIC_G(TAG, 128, 8, 2, 4, 2, LD_F32, EP, DT_F32X), LIC_G(TAG, 128, 8, 1, 4, 2, LD_F32, EP, DT_F32X),        \
+        LIC_G(TAG, 192, 12, 1, 8, 2, LD_F32, EP, DT_F32X)
+#define LIC_GB(TAG, EP)                                                                                        \
+    LIC_G(TAG, 128, 8, 2, 4, 4, LD_F32, EP, DT_BF16), LIC_G(TAG, 128, 8, 1, 4, 4, LD_F32, EP, DT_BF16),        \
+        LIC_G(TAG, 192, 12, 2, 4, 3, LD_F32, EP, DT_BF16), LIC_G(TAG, 192, 12, 1, 4, 4, LD_F32, EP, DT_BF16)
+#define LIC_GF(TAG, EP)                                                                                        \
+    LIC_G(TAG, 128, 8, 2, 4, 2, LD_F32, EP, DT_FP8), LIC_G(TAG, 128, 8, 1, 4, 3, LD_F32, EP, DT_FP8),          \
+        LIC_G(TAG, 192, 12, 2, 4, 2, LD_F32, EP, DT_FP8), LIC_G(TAG, 192, 12, 1, 4, 2, LD_F32, EP, DT_FP8)
+
+static const GdnEntry kGdn[] = {
+    LIC_GX(LIC_GA1, EP_GDN), LIC_GX(LIC_GA2, EP_GDN), LIC_GX(LIC_GS1, EP_IGDN), LIC_GX(LIC_GS2, EP_IGDN),
+    LIC_GB(LIC_GA1, EP_GDN), LIC_GB(LIC_GA2, EP_GDN), LIC_GB(LIC_GS1, EP_IGDN), LIC_GB(LIC_GS2, EP_IGDN),
+    LIC_GF(LIC_GA1, EP_GDN), LIC_GF(LIC_GA2, EP_GDN), LIC_GF(LIC_GS1, EP_IGDN), LIC_GF(LIC_GS2, EP_IGDN),
+    // g_s from symbols, and from y_hat (context model)
+    LIC_G(LIC_GS0, 192, 8, 2, 4, 2, LD_I8, EP_IGDN, DT_F32X), LIC_G(LIC_GS0, 192, 8, 1, 4, 2, LD_I8, EP_IGDN, DT_F32X),
+    LIC_G(LIC_GS0, 192, 8, 2, 4, 4, LD_I8, EP_IGDN, DT_BF16), LIC_G(LIC_GS0, 192, 8, 1, 4, 4, LD_I8, EP_IGDN, DT_BF16),
+    LIC_G(LIC_GS0, 192, 8, 2, 4, 2, LD_F32, EP_IGDN, DT_F32X), LIC_G(LIC_GS0, 192, 8, 1, 4, 2, LD_F32, EP_IGDN, DT_F32X),
+    LIC_G(LIC_GS0, 192, 8, 2, 4, 4, LD_F32, EP_IGDN, DT_BF16), LIC_G(LIC_GS0, 192, 8, 1, 4, 4, LD_F32, EP_IGDN, DT_BF16),
+    LIC_G(LIC_GS0, 320, 12, 1, 8, 2, LD_I8, EP_IGDN, DT_F32X), LIC_G(LIC_GS0, 320, 12, 1, 4, 4, LD_I8, EP_IGDN, DT_BF16),
+};
+
+bool gdn_available(const KernelKey& k)
+{
+    for (const auto& e : kGdn)
+        if (e.key == k) return true;
+    return false;
+}
+
+hipError_t launch_gdn(const KernelKey& k, const ConvArgs& args, int nblocks, hipStream_t stream)
+{
+    for (const auto& e : kGdn)
+        if (e.key == k) {
+            hipLaunchKernelGGL(e.fn, dim3(nblocks), dim3(64 * k.waves), 0, stream, args);
+            return hipGetLastError();
+        }
+    return hipErrorInvalidDeviceFunction;
+}
+
+}  // namespace lic

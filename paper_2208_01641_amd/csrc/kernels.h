@@ -21,6 +21,9 @@ struct KernelKey {
 };
 
 bool kernel_available(const KernelKey& k);
+// GDN layers of whole frames with both operands staged in LDS (gdn_kernels.hip)
+bool gdn_available(const KernelKey& k);
+hipError_t launch_gdn(const KernelKey& k, const ConvArgs& args, int nblocks, hipStream_t stream);
 hipError_t launch_conv(const KernelKey& k, const ConvArgs& args, int nblocks, hipStream_t stream);
 
 // Context model, element-wise steps of the two checkerboard passes (layout

@@ -132,6 +132,23 @@ std::vector<uint16_t> gdn_gamma_split(const std::vector<double>& gamma, int co)
     return out;
 }
 
+// The first `parts` parts of gdn_gamma_split in fragment order
+// [p][16-row block][part][lane][8] (ConvArgs::gt).
+std::vector<uint16_t> gdn_gamma_tiles(const std::vector<uint16_t>& gsplit, int co, int parts)
+{
+    const int npair = co / 32;
+    std::vector<uint16_t> out;
+    out.reserve((size_t)parts * co * co);
+    for (int p = 0; p < npair; ++p)
+        for (int mt = 0; mt < co / 16; ++mt)
+            for (int g = 0; g < parts; ++g)
+                for (int l = 0; l < 64; ++l) {
+                    const size_t j = ((((size_t)g * co + mt * 16 + l % 16) * npair + p) * 4 + l / 16) * 8;
+                    out.insert(out.end(), gsplit.begin() + j, gsplit.begin() + j + 8);
+                }
+    return out;
+}
+
 // OCP e4m3 (1 sign, 4 exponent bits with bias 7, 3 mantissa bits; largest
 // finite 448, subnormal step 2^-9, no infinities) of f, rounding to nearest
 // even and saturating at +-448.
@@ -462,9 +479,11 @@ int Codec::build_layers(const ParamMap& P)
         L.d_bias = (float*)dev_alloc(L.cop * sizeof(float));
         if (!L.d_w || !L.d_ph || !L.d_bias) { err = "device allocation failed"; return LIC_E_NOMEM; }
         std::vector<float> wp(total);
+        std::vector<uint16_t> hb, hx;                    // bf16 / split-FP32 / e4m3 operands
+        std::vector<uint8_t> h8;
         for (size_t j = 0; j < total; ++j) wp[j] = pm.idx[j] < 0 ? 0.0f : (float)w[pm.idx[j]];
         if (L.dt == DT_BF16) {
-            std::vector<uint16_t> hb(total);
+            hb.resize(total);
             for (size_t j = 0; j < total; ++j) hb[j] = bf16_rne(wp[j]);
             HIP_TRY(hipMemcpy(L.d_w, hb.data(), total * esz, hipMemcpyHostToDevice));
         } else if (L.dt == DT_FP8) {
@@ -483,7 +502,7 @@ int Codec::build_layers(const ParamMap& P)
             }
             std::vector<float> wsc(L.cop);
             for (int r = 0; r < L.cop; ++r) wsc[r] = amax[r] > 0.0 ? (float)(amax[r] / 448.0) : 1.0f;
-            std::vector<uint8_t> h8(total);
+            h8.resize(total);
             for (size_t i = 0; i < ph.size(); ++i) {
                 const size_t end = i + 1 < ph.size() ? pm.off[i + 1] : total;
                 for (size_t j = pm.off[i]; j < end; ++j) h8[j] = e4m3_rne(wp[j] / wsc[((j - pm.off[i]) / cin) % (size_t)L.cop]);
@@ -502,7 +521,7 @@ int Codec::build_layers(const ParamMap& P)
                 // 8 packed values as [part 0 x8][part 1 x8][part 2 x8], the
                 // parts rounded to nearest from what the previous ones leave
                 if (total % 8 != 0) { err = std::string("packing mismatch in ") + sp.name; return LIC_E_MODEL; }
-                std::vector<uint16_t> hx(3 * total);
+                hx.resize(3 * total);
                 for (size_t j = 0; j < total; ++j) {
                     float rem = wp[j];
                     for (int g = 0; g < 3; ++g) {
@@ -520,6 +539,26 @@ int Codec::build_layers(const ParamMap& P)
             }
         }
         for (size_t i = 0; i < ph.size(); ++i) ph[i].woff = (int64_t)pm.off[i];
+        if ((sp.ep == EP_GDN || sp.ep == EP_IGDN) && sp.ld != LD_RGB) {
+            // the same operands in fragment order for the staged kernels
+            const int form = L.dt == DT_F32 ? DT_F32X : L.dt;
+            const TileOrder to = tile_order(pm, form);
+            const size_t es = form == DT_FP8 ? 1 : 2;
+            std::vector<uint8_t> wt(to.idx.size() * es);
+            for (size_t j = 0; j < to.idx.size(); ++j) {
+                const int32_t x = to.idx[j];
+                if (form == DT_FP8) {
+                    wt[j] = x < 0 ? 0 : h8[x];
+                } else {
+                    const uint16_t v = form == DT_BF16 ? hb[x] : hx[24 * (x / 8) + 8 * ((j / 512) % 3) + x % 8];
+                    memcpy(&wt[2 * j], &v, 2);
+                }
+            }
+            L.d_wt = (uint8_t*)dev_alloc(wt.size());
+            if (!L.d_wt) { err = "device allocation failed"; return LIC_E_NOMEM; }
+            HIP_TRY(hipMemcpy(L.d_wt, wt.data(), wt.size(), hipMemcpyHostToDevice));
+            for (size_t i = 0; i < ph.size(); ++i) ph[i].wtoff = (int64_t)(to.off[i] * es);
+        }
         HIP_TRY(hipMemcpy(L.d_ph, ph.data(), ph.size() * sizeof(PhaseDesc), hipMemcpyHostToDevice));
         L.host_ph = ph;
         L.halo1 = sp.ld != LD_RGB;
@@ -547,6 +586,10 @@ int Codec::build_layers(const ParamMap& P)
             if (!L.d_gsplit || !L.d_beta) { err = "device allocation failed"; return LIC_E_NOMEM; }
             HIP_TRY(hipMemcpy(L.d_gsplit, g.data(), g.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
             HIP_TRY(hipMemcpy(L.d_beta, be.data(), be.size() * sizeof(float), hipMemcpyHostToDevice));
+            const std::vector<uint16_t> gt = gdn_gamma_tiles(g, co, L.dt == DT_F32 ? 3 : 2);
+            L.d_gt = (uint16_t*)dev_alloc(gt.size() * sizeof(uint16_t));
+            if (!L.d_gt) { err = "device allocation failed"; return LIC_E_NOMEM; }
+            HIP_TRY(hipMemcpy(L.d_gt, gt.data(), gt.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
         }
         // offsets: quantisation of y (factorized: channel medians; hyperprior: 0)
         // and of z (medians); dequantisation in the loaders likewise
@@ -664,6 +707,8 @@ int Codec::launch_layer(int id, int n, const FrameDims& d, const void* in, void*
     a.ph = L.d_ph;
     a.w = L.d_w;
     a.wx = L.d_wx;
+    a.wt = L.d_wt;
+    a.gt = L.d_gt;
     a.zero = d_zero;
     a.bias = L.d_bias;
     a.mu_in = L.d_mu_in;
@@ -716,23 +761,34 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
 {
     KernelKey key{L.tag, L.cin, 0, 0, 0, 1, L.ld, L.ep, L.dt};
     const long pixels = (long)a.n * a.Hg * a.Wg;
+    bool staged = false;
     if (L.ep == EP_GDN || L.ep == EP_IGDN) {
         key.mt = L.cop / 16;
         key.nt = key.mt <= 8 ? 2 : 1;
         key.waves = 4;
         a.ncog = 1;
-        // fewer than one wave per SIMD (1024 on the chip) from the pixel
-        // grid of one image: split K over the 4 waves of a block instead
+        // Fewer than one wave per SIMD (1024 on the chip) from the pixel
+        // grid of one image: split K over the 4 waves of a block instead,
+        // unless 16-pixel groups give at least half a wave per SIMD (128
+        // channels; of the e4m3 layers only GA2).  The choice sets the order
+        // of the sums, so it looks at one image only and not at the batch.
         const long img_waves = (policy_pixels + 16 * key.nt - 1) / (16 * key.nt) * L.nphase;
-        if (L.ld != LD_RGB && img_waves < 1024) {
-            // one 16-pixel group per wave first, if that gives at least half
-            // a wave per SIMD (and such a kernel exists); else split K
-            const long waves1 = (policy_pixels + 15) / 16 * L.nphase;
-            KernelKey k1 = key;
-            k1.nt = 1;
-            if (k1.dt == DT_F32 && a.wx) k1.dt = DT_F32X;
-            if (key.nt == 2 && waves1 >= 512 && kernel_available(k1)) key.nt = 1;
-            else key.ksplit = 4;
+        const long waves1 = (policy_pixels + 15) / 16 * L.nphase;
+        if (L.ld != LD_RGB && img_waves < 1024 &&
+            !(key.mt == 8 && waves1 >= 512 && (L.dt != DT_FP8 || L.tag == LIC_GA2)))
+            key.ksplit = 4;
+        if (L.ld != LD_RGB && key.ksplit == 1 && a.wt) {
+            // Both operands staged in LDS, one or two 16-pixel tiles per wave
+            // (the same sums either way).
+            KernelKey ks = key;
+            if (ks.dt == DT_F32) ks.dt = DT_F32X;
+            ks.waves = ks.dt == DT_F32X && ks.mt == 12 ? 8 : 4;
+            ks.nt = (pixels + 31) / 32 * L.nphase >= 1024 ? 2 : 1;
+            if (!gdn_available(ks)) ks.nt = 1;
+            if (gdn_available(ks)) {
+                key = ks;
+                staged = true;
+            }
         }
     } else if (L.ep == EP_RGB) {
         // every row of the transposed convolution to 3 channels in one wave;
@@ -785,12 +841,12 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
     const long nblocks = tiles * L.nphase * a.ncog;
     if (nblocks <= 0 && !chosen) return LIC_OK;
     if (nblocks > (1L << 30)) { *errp = "launch too large"; return LIC_E_BUDGET; }
-    if (!kernel_available(key)) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
+    if (!staged && !kernel_available(key)) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
     if (chosen) {
         *chosen = key;
         return LIC_OK;
     }
-    hipError_t e = launch_conv(key, a, (int)nblocks, s);
+    hipError_t e = staged ? launch_gdn(key, a, (int)nblocks, s) : launch_conv(key, a, (int)nblocks, s);
     if (e != hipSuccess) {
         *errp = std::string("kernel launch failed: ") + hipGetErrorString(e);
         return LIC_E_HIP;

@@ -162,4 +162,35 @@ PackMap pack_map_checkerboard(int ci, int co, int k, int part, bool pair_rows)
     return m;
 }
 
+TileOrder tile_order(const PackMap& m, int dt)
+{
+    TileOrder o;
+    const int kch = dt == DT_F32 ? 16 : dt == DT_FP8 ? 128 : 32;
+    const int ke = dt == DT_F32 ? 4 : dt == DT_FP8 ? 16 : 8;      // elements per 16 bytes
+    const int sub = dt == DT_F32X ? 3 : dt == DT_FP8 ? 2 : 1;
+    for (size_t f = 0; f < m.ph.size(); ++f) {
+        o.off.push_back(o.idx.size());
+        const int ntaps = m.ph[f].ntaps;
+        const int nk = dt == DT_FP8 ? (ntaps * m.cin + kch - 1) / kch : ntaps * (m.cin / kch);
+        for (int k = 0; k < nk; ++k)
+            for (int mt = 0; mt < m.cop / 16; ++mt)
+                for (int s = 0; s < sub; ++s)
+                    for (int l = 0; l < 64; ++l)
+                        for (int e = 0; e < ke; ++e) {
+                            int t, c;
+                            if (dt == DT_FP8) {
+                                const int x = k * kch + (l / 16) * 32 + s * 16 + e;
+                                t = x / m.cin;
+                                c = x % m.cin;
+                            } else {
+                                t = k % ntaps;
+                                c = (k / ntaps) * kch + (l / 16) * ke + e;
+                            }
+                            const size_t j = m.off[f] + ((size_t)t * m.cop + mt * 16 + l % 16) * m.cin + c;
+                            o.idx.push_back(t < ntaps ? (int32_t)j : -1);
+                        }
+    }
+    return o;
+}
+
 }  // namespace lic

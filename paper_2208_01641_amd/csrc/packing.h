@@ -48,4 +48,20 @@ PackMap pack_map(PackKind kind, int ci, int co, int k, int s, int p, bool w_deco
 // 2 c + 1 hold output channels c and co/2 + c (mean and scale of latent c).
 PackMap pack_map_checkerboard(int ci, int co, int k, int part, bool pair_rows);
 
+// Fragment order of a layer's packed weights: what one MFMA lane holds of a
+// K chunk is 16 consecutive bytes, the 64 lanes of a fragment 1 KB, and the
+// fragments follow each other in the order the K loop uses them:
+//   [phase][chunk][16-row block][sub][lane][16 bytes].
+// Chunks run channel slice outer, tap inner (e4m3: over the flattened (tap,
+// channel) axis, zero past its end); lane l holds row l % 16 of the block and
+// the elements of lane group l / 16.  sub: the three bf16 parts of split-FP32,
+// the two 16-byte halves of e4m3, else one.  Returns for every element its
+// index in the packed array (e4m3 past the end: -1; split-FP32: the FP32
+// element, once per part) and the element offset of each phase.
+struct TileOrder {
+    std::vector<int32_t> idx;
+    std::vector<size_t> off;
+};
+TileOrder tile_order(const PackMap& m, int dt);
+
 }  // namespace lic
