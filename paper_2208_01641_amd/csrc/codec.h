@@ -41,7 +41,8 @@ struct LayerGPU {
     PhaseDesc* d_ph = nullptr;
     uint8_t* d_w = nullptr;            // packed weights (float, bf16 or e4m3)
     uint16_t* d_wx = nullptr;          // FP32 GDN layers: the same as three bf16 parts (ConvArgs::wx)
-    uint8_t* d_wt = nullptr;           // weights in fragment order (ConvArgs::wt)
+    uint8_t* d_wt = nullptr;           // weights in fragment order (ConvArgs::wt, ws)
+    uint8_t* d_ws = nullptr;
     uint16_t* d_gt = nullptr;          // gamma in fragment order (ConvArgs::gt)
     float* d_bias = nullptr;
     float* d_rscale = nullptr;         // e4m3 form: per packed row, weight scale x input scale

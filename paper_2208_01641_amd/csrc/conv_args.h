@@ -55,10 +55,10 @@ enum DType : int {
 struct PhaseDesc {
     int32_t ntaps;
     int32_t oy, ox;          // output position = s_out * grid + (oy, ox)
-    int32_t pad_;
+    int32_t nx;              // taps in rows of nx that share dy, with the same dx in every row (0: no such order)
     int64_t woff;            // element offset of this phase's packed weights
                              // [ntaps][CoP][CIN] from ConvArgs::w
-    int64_t wtoff;           // byte offset of its fragment-order weights from ConvArgs::wt
+    int64_t wtoff;           // element offset of its weights in fragment order (ConvArgs::wt, ws)
     int8_t dy[32], dx[32];   // tap offsets: input = s_in * grid + (dy, dx)
 };
 
@@ -70,7 +70,9 @@ struct ConvArgs {
     const void* w;           // packed weights of every phase (float, bf16 or e4m3)
     const void* wx;          // the same as bf16 parts for DT_F32X (or null): per 8 channels
                              // [part 0 x8][part 1 x8][part 2 x8], offsets 3 x those of w
-    const void* wt;          // weights in fragment order (or null), see tile_order in packing.h
+    const void* wt;          // weights in fragment order (tile_order in packing.h) or null: of the
+                             // staged GDN kernels (FP32: as bf16 parts),
+    const void* ws;          // of the split-K kernels
     const void* gt;          // gamma in fragment order (or null): [p][mt][part][lane][8] bf16, the
                              // parts of gamma[16 mt + lane%16][(2p + i/4) 16 + 4 (lane/16) + i%4]
     const void* zero;        // >= 64 zero bytes: the source of out-of-image reads
@@ -81,6 +83,7 @@ struct ConvArgs {
     const float* beta;       // GDN [Co]
     const float* qmu;        // EP_QUANT offsets [Co]
     const float* thr;        // EP_INDEX thresholds [63]
+    int cin;                 // input channels per tap (kernels without a template CIN)
     int n, Hin, Win;         // input tensor (per image)
     int Hg, Wg, s_in;        // GEMM pixel grid (per image)
     int Hout, Wout, s_out;   // output tensor (per image)

@@ -34,7 +34,7 @@
 // The stride-1 output layer stages halo tiles (a block's rows of
 // pixels with a one-pixel border) and the weights in LDS per channel slice.
 // Small grids split K over the waves of a block with a fixed-order LDS
-// reduction.
+// reduction (the codec's layers: split_kernels.hip).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -853,7 +853,7 @@ conv_igemm(ConvArgs a)
         // group kg holds channel (2p + i/4) 16 + 4 kg + i%4, which is exactly
         // this lane's accumulator element, and gamma's parts are stored in
         // the same channel order.
-        static_assert(MT % 2 == 0, "GDN rows come in 32-channel pairs");
+        static_assert(MT % 2 == 0 && kGLds, "GDN rows come in 32-channel pairs, gamma through LDS");
         constexpr int GP = kGP;                     // bf16 parts per operand
         const bf16x8* __restrict__ gsp = static_cast<const bf16x8*>(a.gsplit);
         constexpr int NPAIR = MT / 2;
@@ -921,10 +921,7 @@ conv_igemm(ConvArgs a)
                 bf16x8 G[GP];
 #pragma unroll
                 for (int g = 0; g < GP; ++g) {
-                    if constexpr (kGLds)
-                        G[g] = __builtin_bit_cast(bf16x8, gbuf[(p & 1) * SCH + (g * MT * 16 + mt * 16 + l16) * 4 + kg]);
-                    else
-                        G[g] = gsp[((long)(g * a.Co + mt * 16 + l16) * NPAIR + p) * 4 + kg];
+                    G[g] = __builtin_bit_cast(bf16x8, gbuf[(p & 1) * SCH + (g * MT * 16 + mt * 16 + l16) * 4 + kg]);
                 }
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
@@ -1129,75 +1126,49 @@ struct KernelEntry {
 #define LIC_K(TAG, CIN, MT, NT, WV, LD, EP) LIC_KS(TAG, CIN, MT, NT, WV, 1, LD, EP)
 // bf16 operand variants of the analysis / synthesis layers
 #define LIC_KB(TAG, CIN, MT, NT, WV, LD, EP) LIC_KSD(TAG, CIN, MT, NT, WV, 1, LD, EP, DT_BF16)
-#define LIC_KGB(TAG, CIN, MT, NT, LD, EP) LIC_KSD(TAG, CIN, MT, NT, 4, 4, LD, EP, DT_BF16)
+// 64 x 32 tiles, four pixel-parallel waves
+#define LIC_KU(TAG, CIN, LD, EP, DT) LIC_KSD(TAG, CIN, 4, 2, 4, 1, LD, EP, DT)
 #define LIC_K2B(TAG, CIN, LD, EP)                                                                \
     LIC_KSD(TAG, CIN, 4, 2, 4, 1, LD, EP, DT_BF16), LIC_KSD(TAG, CIN, 4, 2, 4, 4, LD, EP, DT_BF16), \
         LIC_KSD(TAG, CIN, 4, 2, 8, 8, LD, EP, DT_BF16), LIC_KSD(TAG, CIN, 1, 1, 8, 8, LD, EP, DT_BF16)
 // split-FP32 operands: whole-frame GDN layers of the FP32 form
 #define LIC_KX(TAG, CIN, MT, NT, LD, EP) LIC_KSD(TAG, CIN, MT, NT, 4, 1, LD, EP, DT_F32X)
-// e4m3 operand variants (precision form): g_a and g_s
-#define LIC_KGF(TAG, CIN, MT, NT, LD, EP) LIC_KSD(TAG, CIN, MT, NT, 4, 4, LD, EP, DT_FP8)
-#define LIC_K2F(TAG, CIN, LD, EP)                                                              \
-    LIC_KSD(TAG, CIN, 4, 2, 4, 1, LD, EP, DT_FP8), LIC_KSD(TAG, CIN, 4, 2, 4, 4, LD, EP, DT_FP8), \
-        LIC_KSD(TAG, CIN, 4, 2, 8, 8, LD, EP, DT_FP8), LIC_KSD(TAG, CIN, 1, 1, 8, 8, LD, EP, DT_FP8)
 // the tile configurations of a non-GDN layer: large (4 m-tiles x 2 n-tiles,
 // 4 pixel-parallel waves), large with 4-way split-K, and small (1 x 1) with
 // 8-way split-K, for grids too small to fill the chip
-// GDN / IGDN layers of small grids: 4-way split-K with the normalisation done
-// by the first wave after the reduction (whole frames: gdn_kernels.hip)
-#define LIC_KG(TAG, CIN, MT, NT, LD, EP) LIC_KS(TAG, CIN, MT, NT, 4, 4, LD, EP)
 #define LIC_K2(TAG, CIN, LD, EP)                                                               \
     LIC_K(TAG, CIN, 4, 2, 4, LD, EP), LIC_KS(TAG, CIN, 4, 2, 4, 4, LD, EP), LIC_KS(TAG, CIN, 4, 2, 8, 8, LD, EP), \
         LIC_KS(TAG, CIN, 1, 1, 8, 8, LD, EP)
 
 static const KernelEntry kEntries[] = {
-    // g_a: GDN layers hold every channel of their pixels in one wave (split-K
-    // variants for grids that would leave SIMDs idle)
+    // g_a: the image layer holds every channel of its pixels in one wave (the
+    // other GDN layers: gdn_kernels.hip, split_kernels.hip)
     LIC_K(LIC_GA0, 96, 8, 2, 4, LD_RGB, EP_GDN), LIC_K(LIC_GA0, 96, 12, 1, 4, LD_RGB, EP_GDN),
-    LIC_KG(LIC_GA1, 128, 8, 2, LD_F32, EP_GDN), LIC_KG(LIC_GA1, 192, 12, 1, LD_F32, EP_GDN),
-    LIC_KG(LIC_GA2, 128, 8, 2, LD_F32, EP_GDN), LIC_KG(LIC_GA2, 192, 12, 1, LD_F32, EP_GDN),
-    LIC_K2(LIC_GA3, 128, LD_F32, EP_QUANT), LIC_K2(LIC_GA3, 192, LD_F32, EP_QUANT),
-    // h_a
-    LIC_K2(LIC_HA0, 192, LD_F32_ABS, EP_RELU), LIC_K2(LIC_HA0, 320, LD_F32_ABS, EP_RELU),
-    LIC_K2(LIC_HA1, 128, LD_F32, EP_RELU), LIC_K2(LIC_HA1, 192, LD_F32, EP_RELU),
-    LIC_K2(LIC_HA2, 128, LD_F32, EP_QUANT), LIC_K2(LIC_HA2, 192, LD_F32, EP_QUANT),
-    // h_s
-    LIC_K2(LIC_HS0, 128, LD_I8, EP_RELU), LIC_K2(LIC_HS0, 192, LD_I8, EP_RELU),
-    LIC_K2(LIC_HS1, 128, LD_F32, EP_RELU), LIC_K2(LIC_HS1, 192, LD_F32, EP_RELU),
-    LIC_K2(LIC_HS2, 128, LD_F32, EP_INDEX), LIC_K2(LIC_HS2, 192, LD_F32, EP_INDEX),
-    // context model (N = 128, M = 192): h_a on y, h_s to psi, the context
-    // convolution, the entropy-parameter layers of both passes, g_s from y_hat
-    LIC_K2(LIC_HA0, 192, LD_F32, EP_RELU), LIC_K2(LIC_HS2, 128, LD_F32, EP_NONE),
-    LIC_K2(LIC_CX, 192, LD_F32, EP_NONE),
-    LIC_K2(LIC_EP0A, 768, LD_F32, EP_RELU), LIC_K2(LIC_EP1A, 640, LD_F32, EP_RELU),
-    LIC_K2(LIC_EP2A, 512, LD_F32, EP_MSCALE),
-    LIC_K2(LIC_EP0N, 768, LD_F32, EP_RELU), LIC_K2(LIC_EP1N, 640, LD_F32, EP_RELU),
-    LIC_K2(LIC_EP2N, 512, LD_F32, EP_MSCALE),
-    LIC_KG(LIC_GS0, 192, 8, 2, LD_F32, EP_IGDN), LIC_KGB(LIC_GS0, 192, 8, 2, LD_F32, EP_IGDN),
-    // g_s
-    LIC_KG(LIC_GS0, 192, 8, 2, LD_I8, EP_IGDN), LIC_KG(LIC_GS0, 320, 12, 1, LD_I8, EP_IGDN),
-    LIC_KG(LIC_GS1, 128, 8, 2, LD_F32, EP_IGDN), LIC_KG(LIC_GS1, 192, 12, 1, LD_F32, EP_IGDN),
-    LIC_KG(LIC_GS2, 128, 8, 2, LD_F32, EP_IGDN), LIC_KG(LIC_GS2, 192, 12, 1, LD_F32, EP_IGDN),
+    LIC_KX(LIC_GA0, 96, 8, 2, LD_RGB, EP_GDN), LIC_KX(LIC_GA0, 96, 12, 1, LD_RGB, EP_GDN),
+    LIC_KB(LIC_GA0, 96, 8, 2, 4, LD_RGB, EP_GDN), LIC_KB(LIC_GA0, 96, 12, 1, 4, LD_RGB, EP_GDN),
+    // the other layers of frames so large that K need not be split (split K:
+    // split_kernels.hip)
+    LIC_KU(LIC_GA3, 128, LD_F32, EP_QUANT, DT_F32), LIC_KU(LIC_GA3, 192, LD_F32, EP_QUANT, DT_F32),
+    LIC_KU(LIC_GA3, 128, LD_F32, EP_QUANT, DT_BF16), LIC_KU(LIC_GA3, 192, LD_F32, EP_QUANT, DT_BF16),
+    LIC_KU(LIC_GA3, 128, LD_F32, EP_QUANT, DT_FP8), LIC_KU(LIC_GA3, 192, LD_F32, EP_QUANT, DT_FP8),
+    LIC_KU(LIC_HA0, 192, LD_F32_ABS, EP_RELU, DT_F32), LIC_KU(LIC_HA0, 320, LD_F32_ABS, EP_RELU, DT_F32),
+    LIC_KU(LIC_HA1, 128, LD_F32, EP_RELU, DT_F32), LIC_KU(LIC_HA1, 192, LD_F32, EP_RELU, DT_F32),
+    LIC_KU(LIC_HA2, 128, LD_F32, EP_QUANT, DT_F32), LIC_KU(LIC_HA2, 192, LD_F32, EP_QUANT, DT_F32),
+    LIC_KU(LIC_HS0, 128, LD_I8, EP_RELU, DT_F32), LIC_KU(LIC_HS0, 192, LD_I8, EP_RELU, DT_F32),
+    LIC_KU(LIC_HS1, 128, LD_F32, EP_RELU, DT_F32), LIC_KU(LIC_HS1, 192, LD_F32, EP_RELU, DT_F32),
+    LIC_KU(LIC_HS2, 128, LD_F32, EP_INDEX, DT_F32), LIC_KU(LIC_HS2, 192, LD_F32, EP_INDEX, DT_F32),
+    // context model (N = 128, M = 192)
+    LIC_KU(LIC_HA0, 192, LD_F32, EP_RELU, DT_F32), LIC_KU(LIC_HS2, 128, LD_F32, EP_NONE, DT_F32),
+    LIC_KU(LIC_CX, 192, LD_F32, EP_NONE, DT_F32),
+    LIC_KU(LIC_EP0A, 768, LD_F32, EP_RELU, DT_F32), LIC_KU(LIC_EP1A, 640, LD_F32, EP_RELU, DT_F32),
+    LIC_KU(LIC_EP2A, 512, LD_F32, EP_MSCALE, DT_F32),
+    LIC_KU(LIC_EP0N, 768, LD_F32, EP_RELU, DT_F32), LIC_KU(LIC_EP1N, 640, LD_F32, EP_RELU, DT_F32),
+    LIC_KU(LIC_EP2N, 512, LD_F32, EP_MSCALE, DT_F32),
+    // g_s's output layer
     LIC_K(LIC_GS3, 128, 1, 4, 4, LD_F32, EP_RGB), LIC_K(LIC_GS3, 192, 1, 4, 4, LD_F32, EP_RGB),
     LIC_K(LIC_GS3, 128, 1, 4, 4, LD_TILE, EP_RGB), LIC_K(LIC_GS3, 192, 1, 4, 4, LD_TILE, EP_RGB),
-    LIC_KX(LIC_GA0, 96, 8, 2, LD_RGB, EP_GDN), LIC_KX(LIC_GA0, 96, 12, 1, LD_RGB, EP_GDN),
-    // bf16 operands (precision form): g_a and g_s; h_a / h_s stay FP32
-    LIC_KB(LIC_GA0, 96, 8, 2, 4, LD_RGB, EP_GDN), LIC_KB(LIC_GA0, 96, 12, 1, 4, LD_RGB, EP_GDN),
-    LIC_KGB(LIC_GA1, 128, 8, 2, LD_F32, EP_GDN), LIC_KGB(LIC_GA1, 192, 12, 1, LD_F32, EP_GDN),
-    LIC_KGB(LIC_GA2, 128, 8, 2, LD_F32, EP_GDN), LIC_KGB(LIC_GA2, 192, 12, 1, LD_F32, EP_GDN),
-    LIC_K2B(LIC_GA3, 128, LD_F32, EP_QUANT), LIC_K2B(LIC_GA3, 192, LD_F32, EP_QUANT),
-    LIC_KGB(LIC_GS0, 192, 8, 2, LD_I8, EP_IGDN), LIC_KGB(LIC_GS0, 320, 12, 1, LD_I8, EP_IGDN),
-    LIC_KGB(LIC_GS1, 128, 8, 2, LD_F32, EP_IGDN), LIC_KGB(LIC_GS1, 192, 12, 1, LD_F32, EP_IGDN),
-    LIC_KGB(LIC_GS2, 128, 8, 2, LD_F32, EP_IGDN), LIC_KGB(LIC_GS2, 192, 12, 1, LD_F32, EP_IGDN),
     LIC_KB(LIC_GS3, 128, 1, 4, 4, LD_F32, EP_RGB), LIC_KB(LIC_GS3, 192, 1, 4, 4, LD_F32, EP_RGB),
     LIC_KB(LIC_GS3, 128, 1, 4, 4, LD_TILE, EP_RGB), LIC_KB(LIC_GS3, 192, 1, 4, 4, LD_TILE, EP_RGB),
-    // e4m3 operands (precision form): g_a and g_s
-    LIC_KGF(LIC_GA1, 128, 8, 2, LD_F32, EP_GDN), LIC_KGF(LIC_GA1, 192, 12, 1, LD_F32, EP_GDN),
-    LIC_KGF(LIC_GA2, 128, 8, 2, LD_F32, EP_GDN), LIC_KGF(LIC_GA2, 192, 12, 1, LD_F32, EP_GDN),
-    LIC_K2F(LIC_GA3, 128, LD_F32, EP_QUANT), LIC_K2F(LIC_GA3, 192, LD_F32, EP_QUANT),
-    // (g_s's first layer runs on bf16 operands in this form: no e4m3 kernel)
-    LIC_KGF(LIC_GS1, 128, 8, 2, LD_F32, EP_IGDN), LIC_KGF(LIC_GS1, 192, 12, 1, LD_F32, EP_IGDN),
-    LIC_KGF(LIC_GS2, 128, 8, 2, LD_F32, EP_IGDN), LIC_KGF(LIC_GS2, 192, 12, 1, LD_F32, EP_IGDN),
     // distilled synthesis network (64 hidden channels): forward in FP32 or
     // bf16 operands, input gradients (ReLU-masked) in FP32
     LIC_K2(TAG_DT1, 192, LD_I8, EP_RELU), LIC_K2(TAG_DT1, 320, LD_I8, EP_RELU),

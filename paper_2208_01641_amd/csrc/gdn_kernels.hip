@@ -34,33 +34,12 @@
 #include "../../include/lic.h"
 #include "conv_args.h"
 #include "kernels.h"
+#include "lds_stage.h"
 #include "mfma_common.h"
 
 namespace lic {
 
-// s_waitcnt vmcnt(N) alone (expcnt and lgkmcnt at their maxima)
-template <int N> __device__ __forceinline__ void wait_vm()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-
-// workgroup barrier that orders LDS accesses only: loads into LDS that are
-// still in flight are waited for by wait_vm where their stage is used
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// orders one wave's LDS accesses before and after (lanes read each other's)
-__device__ __forceinline__ void wave_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+template <int I> using Int = std::integral_constant<int, I>;
 
 // WAVES: 4 with two blocks per CU, or 8 with one where two blocks' stages do
 // not fit its 160 KB of LDS (either way two waves per SIMD, 256 registers).
@@ -105,7 +84,7 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
     const int ntaps = ph->ntaps;
     // lane t keeps the offsets of tap t
     const int tapv = lane < ntaps ? (((int)ph->dy[lane] & 0xffff) | ((int)ph->dx[lane] << 16)) : 0;
-    const uint8_t* __restrict__ wt = static_cast<const uint8_t*>(a.wt) + ph->wtoff;
+    const Buf wbuf = make_buf(static_cast<const uint8_t*>(a.wt) + ph->wtoff * (DT == DT_F32X ? 6 : (int)sizeof(typename Prec<DT>::WElem)));
     const int HWg = a.Hg * a.Wg;
     const int total = a.n * HWg;
     const int pix0 = (tile * WAVES + wave) * (NT * 16);
@@ -114,25 +93,32 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
     // A pixel past the end gets an origin no tap brings into the image.
     const int lpx = lane / LPR, slot = lane % LPR;
     auto rot = [](int p) { return LPR == 2 ? 0 : LPR == 4 ? (p >> 1) & 3 : ((p >> 1) & 1) | (((p >> 2) & 1) << 2); };
-    int oy0[NB], ox0[NB], pc[NB];
-    const uint8_t* pb[NB];
+    // byte offsets count from the wave's first pixel's row (pixels follow each
+    // other in memory, so they are small whatever the tensor's size); bit t of
+    // bad: tap t falls outside the image (or past the last tap)
+    const int im0 = pix0 / HWg, y0 = (pix0 - im0 * HWg) / a.Wg;
+    const uint8_t* const in0 = static_cast<const uint8_t*>(a.in) + ((long)im0 * a.Hin + y0 * a.s_in) * a.Win * (long)(CIN * ESZ);
+    int pc[NB];
+    uint32_t poff[NB], bad[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int pl = i * PPI + lpx;
         const int p = pl < NT * 16 ? pix0 + pl : total;
-        const int q = p < total ? p : 0;
+        const int q = p < total ? p : pix0;
         const int im = q / HWg, r = q - im * HWg;
         const int y = r / a.Wg, x = r - y * a.Wg;
-        oy0[i] = p < total ? y * a.s_in : -(1 << 20);
-        ox0[i] = x * a.s_in;
+        const int oy = p < total ? y * a.s_in : -(1 << 20), ox = x * a.s_in;
         pc[i] = (slot ^ rot(pl & 15)) * 16;
-        pb[i] = static_cast<const uint8_t*>(a.in) +
-                (((long)im * a.Hin + y * a.s_in) * a.Win + x * a.s_in) * (long)(CIN * ESZ) + (DT == DT_FP8 ? 0 : pc[i]);
+        poff[i] = (uint32_t)((((long)(im - im0) * a.Hin + (y - y0) * a.s_in) * a.Win + ox) * (CIN * ESZ)) +
+                  (uint32_t)pc[i];
+        bad[i] = bad_taps(oy, ox, tapv, ntaps, ph->nx, a.Hin, a.Win);
     }
 
     constexpr int KC = DT == DT_FP8 ? 1 : CIN / KCH;
     const int nk = DT == DT_FP8 ? (ntaps * CIN + KCH - 1) / KCH : ntaps * KC;
     int i_t = 0, i_s = 0, i_k = 0, i_st = 0;             // next chunk to load: tap, channel slice, index, stage
+    const int toffv = ((int)(short)(tapv & 0xffff) * a.Win + (tapv >> 16)) * (CIN * ESZ);   // bytes to tap t
+    auto tap_off = [&](int t) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(toffv, t < ntaps ? t : 0); };
     auto tap = [&](int t, int& dy, int& dx) __attribute__((always_inline)) {
         const int tv = __builtin_amdgcn_readlane(tapv, t < ntaps ? t : 0);
         dy = t < ntaps ? (int)(short)(tv & 0xffff) : -(1 << 20);
@@ -140,53 +126,28 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
     };
     auto issue = [&]() __attribute__((always_inline)) {
         uint32_t* const st = smem + i_st * STW;
-        const uint8_t* ag = wt + (size_t)i_k * (AP * 1024);
 #pragma unroll
         for (int u = 0; u < AW; ++u) {
             const int f = AP % WAVES == 0 ? wave * AW + u : min(wave * AW + u, AP - 1);
-#if defined(__HIP_DEVICE_COMPILE__)
-            __builtin_amdgcn_global_load_lds(ag + f * 1024 + lane * 16, st + f * 256, 16, 0, 0);
-#endif
-            (void)f;
+            buf_load_lds(wbuf, st + f * 256, lane * 16, (i_k * AP + f) * 1024);
         }
-        int dyA, dxA, dyB = 0, dxB = 0;
-        long offA, offB = 0;
-        int c0 = 0;
+        // a chunk's window is the buffer's base moved by its tap; lanes whose
+        // tap is out of the image read zero
+        uint32_t* const sb = st + (AP + wave * NB) * 256;
         if constexpr (DT == DT_FP8) {
-            const int f0 = i_k * KCH, tA = f0 / CIN;
-            c0 = f0 - tA * CIN;
-            tap(tA, dyA, dxA);
-            offA = ((long)dyA * a.Win + dxA) * CIN + c0;
-            if constexpr (CIN % KCH != 0) {
-                tap(tA + 1, dyB, dxB);
-                offB = ((long)dyB * a.Win + dxB) * CIN + c0 - CIN;
+            const int f0 = i_k * KCH, tA = f0 / CIN, c0 = f0 - tA * CIN;
+            const int step = CIN % KCH != 0 ? tap_off(tA + 1) - CIN - tap_off(tA) : 0;
+            const Buf b = make_buf(in0 + (tap_off(tA) + c0 + min(step, 0)));
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const bool second = CIN % KCH != 0 && c0 + pc[i] >= CIN;
+                buf_load_lds(b, sb + i * 256, (poff[i] + (second ? max(step, 0) : max(-step, 0))) | bit_mask(bad[i], second ? tA + 1 : tA), 0);
             }
         } else {
-            tap(i_t, dyA, dxA);
-            offA = (((long)dyA * a.Win + dxA) * CIN + i_s * KCH) * ESZ;
-        }
+            const Buf b = make_buf(in0 + (tap_off(i_t) + i_s * (KCH * ESZ)));
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            int dy = dyA, dx = dxA;
-            const uint8_t* src = pb[i] + offA;
-            if constexpr (DT == DT_FP8) {
-                if constexpr (CIN % KCH != 0) {
-                    const bool second = c0 + pc[i] >= CIN;
-                    dy = second ? dyB : dyA;
-                    dx = second ? dxB : dxA;
-                    src = pb[i] + (second ? offB : offA);
-                }
-                src += pc[i];
-            }
-            const bool ok = ((unsigned)(oy0[i] + dy) < (unsigned)a.Hin) & ((unsigned)(ox0[i] + dx) < (unsigned)a.Win);
-            src = ok ? src : static_cast<const uint8_t*>(a.zero);
-#if defined(__HIP_DEVICE_COMPILE__)
-            __builtin_amdgcn_global_load_lds(src, st + (AP + wave * NB + i) * 256, 16, 0, 0);
-#endif
-            (void)src;
+            for (int i = 0; i < NB; ++i) buf_load_lds(b, sb + i * 256, poff[i] | bit_mask(bad[i], i_t), 0);
         }
-        (void)ag;
-        (void)st;
         if (++i_t == ntaps) {
             i_t = 0;
             ++i_s;
@@ -337,16 +298,12 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
     // ------------------------------------------------------------ GDN
     // n = beta + gamma (x*x) as in conv_igemm: x*x and gamma in GP bf16 parts,
     // 32 channels per K chunk; gamma slice p = [mt][part][lane][8]
-    const uint8_t* gt = static_cast<const uint8_t*>(a.gt);
+    const Buf gbuf = make_buf(a.gt);
     auto g_issue = [&](int p) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < GW; ++u) {
             const int f = MT * GP % WAVES == 0 ? wave * GW + u : min(wave * GW + u, MT * GP - 1);
-#if defined(__HIP_DEVICE_COMPILE__)
-            __builtin_amdgcn_global_load_lds(gt + ((size_t)p * (MT * GP) + f) * 1024 + lane * 16,
-                                             smem + (p % GSL) * GSW + f * 256, 16, 0, 0);
-#endif
-            (void)f;
+            buf_load_lds(gbuf, smem + (p % GSL) * GSW + f * 256, lane * 16, (p * (MT * GP) + f) * 1024);
         }
     };
     if constexpr (DT == DT_FP8) {
@@ -411,9 +368,10 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
             mul(0, 0);
         }
     };
-    [&]<int... P>(std::integer_sequence<int, P...>) __attribute__((always_inline)) {
-        (pair(std::integral_constant<int, P>{}), ...);
-    }(std::make_integer_sequence<int, NPAIR>{});
+    auto pairs = [&](auto... p) __attribute__((always_inline)) { (pair(p), ...); };
+    static_assert(NPAIR == 4 || NPAIR == 6, "128 or 192 channels");
+    pairs(Int<0>{}, Int<1>{}, Int<2>{}, Int<3>{});
+    if constexpr (NPAIR == 6) pairs(Int<4>{}, Int<5>{});
     lds_barrier();                                      // the last slice has been read
 
     // ------------------------------------------------------------ output

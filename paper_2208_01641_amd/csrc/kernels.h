@@ -24,6 +24,17 @@ bool kernel_available(const KernelKey& k);
 // GDN layers of whole frames with both operands staged in LDS (gdn_kernels.hip)
 bool gdn_available(const KernelKey& k);
 hipError_t launch_gdn(const KernelKey& k, const ConvArgs& args, int nblocks, hipStream_t stream);
+// layers of small grids, split K over the waves of a block (split_kernels.hip):
+// rg groups of mt 16-row blocks x nt 16-pixel tiles, ks K slots
+struct SplitKey {
+    int mt, nt, rg, ks, ld, ep, dt;
+    bool operator==(const SplitKey& o) const
+    {
+        return mt == o.mt && nt == o.nt && rg == o.rg && ks == o.ks && ld == o.ld && ep == o.ep && dt == o.dt;
+    }
+};
+bool split_available(const SplitKey& k);
+hipError_t launch_split(const SplitKey& k, const ConvArgs& args, int nblocks, hipStream_t stream);
 hipError_t launch_conv(const KernelKey& k, const ConvArgs& args, int nblocks, hipStream_t stream);
 
 // Context model, element-wise steps of the two checkerboard passes (layout

@@ -539,25 +539,36 @@ int Codec::build_layers(const ParamMap& P)
             }
         }
         for (size_t i = 0; i < ph.size(); ++i) ph[i].woff = (int64_t)pm.off[i];
-        if ((sp.ep == EP_GDN || sp.ep == EP_IGDN) && sp.ld != LD_RGB) {
-            // the same operands in fragment order for the staged kernels
-            const int form = L.dt == DT_F32 ? DT_F32X : L.dt;
+        // the same operands in fragment order: of the staged kernels (GDN layers;
+        // FP32 as bf16 parts) and of the split-K kernels
+        auto fragments = [&](int form, uint8_t** dst) -> int {
             const TileOrder to = tile_order(pm, form);
-            const size_t es = form == DT_FP8 ? 1 : 2;
+            const size_t es = form == DT_F32 ? 4 : form == DT_FP8 ? 1 : 2, sub = form == DT_F32X ? 3 : 1;
             std::vector<uint8_t> wt(to.idx.size() * es);
             for (size_t j = 0; j < to.idx.size(); ++j) {
                 const int32_t x = to.idx[j];
                 if (form == DT_FP8) {
                     wt[j] = x < 0 ? 0 : h8[x];
+                } else if (form == DT_F32) {
+                    memcpy(&wt[4 * j], &wp[x], 4);
                 } else {
                     const uint16_t v = form == DT_BF16 ? hb[x] : hx[24 * (x / 8) + 8 * ((j / 512) % 3) + x % 8];
                     memcpy(&wt[2 * j], &v, 2);
                 }
             }
-            L.d_wt = (uint8_t*)dev_alloc(wt.size());
-            if (!L.d_wt) { err = "device allocation failed"; return LIC_E_NOMEM; }
-            HIP_TRY(hipMemcpy(L.d_wt, wt.data(), wt.size(), hipMemcpyHostToDevice));
-            for (size_t i = 0; i < ph.size(); ++i) ph[i].wtoff = (int64_t)(to.off[i] * es);
+            *dst = (uint8_t*)dev_alloc(wt.size());
+            if (!*dst) { err = "device allocation failed"; return LIC_E_NOMEM; }
+            HIP_TRY(hipMemcpy(*dst, wt.data(), wt.size(), hipMemcpyHostToDevice));
+            for (size_t i = 0; i < ph.size(); ++i) ph[i].wtoff = (int64_t)(to.off[i] / sub);
+            return LIC_OK;
+        };
+        if (sp.ld != LD_RGB && sp.ep != EP_RGB) {
+            const bool gdn = sp.ep == EP_GDN || sp.ep == EP_IGDN;
+            int rc = LIC_OK;
+            if (gdn) rc = fragments(L.dt == DT_F32 ? DT_F32X : L.dt, &L.d_wt);
+            if (rc == LIC_OK && gdn && L.dt != DT_F32) L.d_ws = L.d_wt;
+            else if (rc == LIC_OK) rc = fragments(L.dt, &L.d_ws);
+            if (rc != LIC_OK) return rc;
         }
         HIP_TRY(hipMemcpy(L.d_ph, ph.data(), ph.size() * sizeof(PhaseDesc), hipMemcpyHostToDevice));
         L.host_ph = ph;
@@ -708,6 +719,8 @@ int Codec::launch_layer(int id, int n, const FrameDims& d, const void* in, void*
     a.w = L.d_w;
     a.wx = L.d_wx;
     a.wt = L.d_wt;
+    a.ws = L.d_ws;
+    a.cin = L.cin;
     a.gt = L.d_gt;
     a.zero = d_zero;
     a.bias = L.d_bias;
@@ -833,20 +846,47 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
             a.w = a.wx;
         }
     }
+    // Split K: the K slots are fixed by the rule above, the tile of a block is
+    // free (the same sums whatever it is): the largest that still gives the
+    // chip enough blocks.  Measured at 720p (us; blocks in brackets): g_a's last
+    // layer 64 x 32 62 [360], 64 x 16 53 [720], 32 x 16 58 [1440]; the same at
+    // 470 x 834 36 [168], 35 [336], 31 [672]; h_a's second 31 [60], 19 [120], 14
+    // [240], 16 x 16 15 [480]; its third 31, 18, 12 [60], 10 [120]; bf16 g_a's
+    // last 18 [360], 21 [720].
+    SplitKey sk{};
+    if (key.ksplit > 1 && a.ws) {
+        const bool gdn = L.ep == EP_GDN || L.ep == EP_IGDN;
+        sk = SplitKey{4, 1, gdn ? key.mt / 4 : 1, key.ksplit, L.ld, L.ep, L.dt};
+        auto blocks = [&](int mt, int nt) { return (pixels + 16 * nt - 1) / (16 * nt) * L.nphase * (gdn ? 1 : L.cop / (16 * mt)); };
+        if (gdn) {
+            // (e4m3, g_s's second layer at 512 x 768: 35 us with 16-pixel
+            // tiles, 26 with 32-pixel tiles)
+            if (blocks(4, 2) >= 512) sk.nt = 2;
+            if (!split_available(sk)) sk.nt = 1;
+        } else if (L.cop % 64 == 0 && blocks(4, 2) >= (L.dt == DT_F32 ? 1024 : 320)) {
+            sk.nt = 2;
+        } else if (L.cop % 64 != 0 || blocks(4, 1) < 448) {
+            sk.mt = L.cop % 32 == 0 && (blocks(2, 1) >= 200 || key.ksplit != 8) ? 2 : 1;
+        }
+        if (split_available(sk)) a.ncog = gdn ? 1 : L.cop / (16 * sk.mt);
+        else sk = SplitKey{};
+    }
     const long per_block = (long)(key.waves / key.ksplit) * key.nt * 16;
     // halo tiles: one block per key.waves grid rows x 16 key.nt pixels
-    const long tiles = key.ld == LD_TILE
+    const long tiles = sk.mt ? (pixels + 16 * sk.nt - 1) / (16 * sk.nt)
+                       : key.ld == LD_TILE
                            ? (long)a.n * ((a.Hg + key.waves - 1) / key.waves) * ((a.Wg + 16 * key.nt - 1) / (16 * key.nt))
                            : (pixels + per_block - 1) / per_block;
     const long nblocks = tiles * L.nphase * a.ncog;
     if (nblocks <= 0 && !chosen) return LIC_OK;
     if (nblocks > (1L << 30)) { *errp = "launch too large"; return LIC_E_BUDGET; }
-    if (!staged && !kernel_available(key)) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
+    if (!staged && !sk.mt && !kernel_available(key)) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
     if (chosen) {
         *chosen = key;
         return LIC_OK;
     }
-    hipError_t e = staged ? launch_gdn(key, a, (int)nblocks, s) : launch_conv(key, a, (int)nblocks, s);
+    hipError_t e = staged ? launch_gdn(key, a, (int)nblocks, s)
+                   : sk.mt ? launch_split(sk, a, (int)nblocks, s) : launch_conv(key, a, (int)nblocks, s);
     if (e != hipSuccess) {
         *errp = std::string("kernel launch failed: ") + hipGetErrorString(e);
         return LIC_E_HIP;

@@ -40,6 +40,7 @@ PackMap pack_map(PackKind kind, int ci, int co, int k, int s, int p, bool w_deco
         m.cop = 16 * ((co + 15) / 16);
         PhaseDesc d{};
         d.ntaps = k * k;
+        d.nx = k;
         for (int u = 0; u < k; ++u)
             for (int v = 0; v < k; ++v) {
                 d.dy[u * k + v] = (int8_t)(u - p);
@@ -65,6 +66,7 @@ PackMap pack_map(PackKind kind, int ci, int co, int k, int s, int p, bool w_deco
                 for (int u = 0; u < k; ++u) if ((py + p - u) % s == 0) us.push_back(u);
                 for (int v = 0; v < k; ++v) if ((px + p - v) % s == 0) vs.push_back(v);
                 d.ntaps = (int)(us.size() * vs.size());
+                d.nx = (int)vs.size();
                 int t = 0;
                 for (int u : us)
                     for (int v : vs) {
@@ -96,6 +98,7 @@ PackMap pack_map(PackKind kind, int ci, int co, int k, int s, int p, bool w_deco
         const int nd = dmax - dmin + 1;
         PhaseDesc d{};
         d.ntaps = nd * nd;
+        d.nx = nd;
         for (int dy = dmin; dy <= dmax; ++dy)
             for (int dx = dmin; dx <= dmax; ++dx) {
                 const int t = (dy - dmin) * nd + (dx - dmin);
