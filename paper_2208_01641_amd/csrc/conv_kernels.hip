@@ -1164,11 +1164,6 @@ static const KernelEntry kEntries[] = {
     LIC_KU(LIC_EP2A, 512, LD_F32, EP_MSCALE, DT_F32),
     LIC_KU(LIC_EP0N, 768, LD_F32, EP_RELU, DT_F32), LIC_KU(LIC_EP1N, 640, LD_F32, EP_RELU, DT_F32),
     LIC_KU(LIC_EP2N, 512, LD_F32, EP_MSCALE, DT_F32),
-    // g_s's output layer
-    LIC_K(LIC_GS3, 128, 1, 4, 4, LD_F32, EP_RGB), LIC_K(LIC_GS3, 192, 1, 4, 4, LD_F32, EP_RGB),
-    LIC_K(LIC_GS3, 128, 1, 4, 4, LD_TILE, EP_RGB), LIC_K(LIC_GS3, 192, 1, 4, 4, LD_TILE, EP_RGB),
-    LIC_KB(LIC_GS3, 128, 1, 4, 4, LD_F32, EP_RGB), LIC_KB(LIC_GS3, 192, 1, 4, 4, LD_F32, EP_RGB),
-    LIC_KB(LIC_GS3, 128, 1, 4, 4, LD_TILE, EP_RGB), LIC_KB(LIC_GS3, 192, 1, 4, 4, LD_TILE, EP_RGB),
     // distilled synthesis network (64 hidden channels): forward in FP32 or
     // bf16 operands, input gradients (ReLU-masked) in FP32
     LIC_K2(TAG_DT1, 192, LD_I8, EP_RELU), LIC_K2(TAG_DT1, 320, LD_I8, EP_RELU),

@@ -562,7 +562,7 @@ int Codec::build_layers(const ParamMap& P)
             for (size_t i = 0; i < ph.size(); ++i) ph[i].wtoff = (int64_t)(to.off[i] / sub);
             return LIC_OK;
         };
-        if (sp.ld != LD_RGB && sp.ep != EP_RGB) {
+        if (sp.ld != LD_RGB) {
             const bool gdn = sp.ep == EP_GDN || sp.ep == EP_IGDN;
             int rc = LIC_OK;
             if (gdn) rc = fragments(L.dt == DT_F32 ? DT_F32X : L.dt, &L.d_wt);
@@ -774,7 +774,7 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
 {
     KernelKey key{L.tag, L.cin, 0, 0, 0, 1, L.ld, L.ep, L.dt};
     const long pixels = (long)a.n * a.Hg * a.Wg;
-    bool staged = false;
+    bool staged = false, rgb = false;
     if (L.ep == EP_GDN || L.ep == EP_IGDN) {
         key.mt = L.cop / 16;
         key.nt = key.mt <= 8 ? 2 : 1;
@@ -810,7 +810,11 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
         key.nt = 4;
         key.waves = 4;
         a.ncog = 1;
-        if (L.halo1 && L.ld == LD_F32) {
+        if (L.halo1 && L.ld == LD_F32 && a.ws && a.s_out == 2 && L.cop == 16 && a.Hg % 8 == 0 && a.Wg % 32 == 0 &&
+            rgb_available(L.cin, L.dt)) {
+            key.ld = LD_TILE;
+            rgb = true;
+        } else if (L.halo1 && L.ld == LD_F32) {
             KernelKey kt = key;
             kt.ld = LD_TILE;
             if (kernel_available(kt)) key = kt;
@@ -880,12 +884,12 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
     const long nblocks = tiles * L.nphase * a.ncog;
     if (nblocks <= 0 && !chosen) return LIC_OK;
     if (nblocks > (1L << 30)) { *errp = "launch too large"; return LIC_E_BUDGET; }
-    if (!staged && !sk.mt && !kernel_available(key)) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
+    if (!staged && !rgb && !sk.mt && !kernel_available(key)) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
     if (chosen) {
         *chosen = key;
         return LIC_OK;
     }
-    hipError_t e = staged ? launch_gdn(key, a, (int)nblocks, s)
+    hipError_t e = rgb ? launch_rgb(L.cin, L.dt, a, s) : staged ? launch_gdn(key, a, (int)nblocks, s)
                    : sk.mt ? launch_split(sk, a, (int)nblocks, s) : launch_conv(key, a, (int)nblocks, s);
     if (e != hipSuccess) {
         *errp = std::string("kernel launch failed: ") + hipGetErrorString(e);
