@@ -1141,11 +1141,10 @@ struct KernelEntry {
         LIC_KS(TAG, CIN, 1, 1, 8, 8, LD, EP)
 
 static const KernelEntry kEntries[] = {
-    // g_a: the image layer holds every channel of its pixels in one wave (the
-    // other GDN layers: gdn_kernels.hip, split_kernels.hip)
-    LIC_K(LIC_GA0, 96, 8, 2, 4, LD_RGB, EP_GDN), LIC_K(LIC_GA0, 96, 12, 1, 4, LD_RGB, EP_GDN),
-    LIC_KX(LIC_GA0, 96, 8, 2, LD_RGB, EP_GDN), LIC_KX(LIC_GA0, 96, 12, 1, LD_RGB, EP_GDN),
-    LIC_KB(LIC_GA0, 96, 8, 2, 4, LD_RGB, EP_GDN), LIC_KB(LIC_GA0, 96, 12, 1, 4, LD_RGB, EP_GDN),
+    // g_a: the image layer at 192 channels holds every channel of its pixels in
+    // one wave (128 channels: image_kernels.hip; the other GDN layers:
+    // gdn_kernels.hip, split_kernels.hip)
+    LIC_KX(LIC_GA0, 96, 12, 1, LD_RGB, EP_GDN), LIC_KB(LIC_GA0, 96, 12, 1, 4, LD_RGB, EP_GDN),
     // the other layers of frames so large that K need not be split (split K:
     // split_kernels.hip)
     LIC_KU(LIC_GA3, 128, LD_F32, EP_QUANT, DT_F32), LIC_KU(LIC_GA3, 192, LD_F32, EP_QUANT, DT_F32),

@@ -38,6 +38,10 @@ hipError_t launch_split(const SplitKey& k, const ConvArgs& args, int nblocks, hi
 // g_s's output layer (rgb_kernels.hip): 3 x 3 neighbourhood, grid a multiple of 8 x 32
 bool rgb_available(int cin, int dt);
 hipError_t launch_rgb(int cin, int dt, const ConvArgs& args, hipStream_t stream);
+// g_a's first layer (image_kernels.hip): 5 x 5, stride 2, 128 channels, grid rows
+// of whole 32-pixel tiles
+bool image_available(int cop, int dt);
+hipError_t launch_image(int dt, const ConvArgs& args, hipStream_t stream);
 hipError_t launch_conv(const KernelKey& k, const ConvArgs& args, int nblocks, hipStream_t stream);
 
 // Context model, element-wise steps of the two checkerboard passes (layout

@@ -59,6 +59,13 @@ __device__ __forceinline__ void buf_load_lds(Buf b, uint32_t* dst, uint32_t lane
     __builtin_amdgcn_raw_ptr_buffer_load_lds(b, (__attribute__((address_space(3))) void*)dst, 16, lane_off, off, 0, 0);
 #endif
 }
+// the same with 4 bytes per lane (lane l to dst + 4 l)
+__device__ __forceinline__ void buf_load_lds4(Buf b, uint32_t* dst, uint32_t lane_off, int off)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(b, (__attribute__((address_space(3))) void*)dst, 4, lane_off, off, 0, 0);
+#endif
+}
 __device__ __forceinline__ u32x4 buf_load(Buf b, uint32_t lane_off, int off)
 {
 #if defined(__HIP_DEVICE_COMPILE__)

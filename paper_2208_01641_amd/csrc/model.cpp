@@ -562,7 +562,10 @@ int Codec::build_layers(const ParamMap& P)
             for (size_t i = 0; i < ph.size(); ++i) ph[i].wtoff = (int64_t)(to.off[i] / sub);
             return LIC_OK;
         };
-        if (sp.ld != LD_RGB) {
+        if (sp.ld == LD_RGB) {
+            const int rc = fragments(L.dt == DT_F32 ? DT_F32X : L.dt, &L.d_ws);
+            if (rc != LIC_OK) return rc;
+        } else {
             const bool gdn = sp.ep == EP_GDN || sp.ep == EP_IGDN;
             int rc = LIC_OK;
             if (gdn) rc = fragments(L.dt == DT_F32 ? DT_F32X : L.dt, &L.d_wt);
@@ -774,7 +777,7 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
 {
     KernelKey key{L.tag, L.cin, 0, 0, 0, 1, L.ld, L.ep, L.dt};
     const long pixels = (long)a.n * a.Hg * a.Wg;
-    bool staged = false, rgb = false;
+    bool staged = false, rgb = false, image = false;
     if (L.ep == EP_GDN || L.ep == EP_IGDN) {
         key.mt = L.cop / 16;
         key.nt = key.mt <= 8 ? 2 : 1;
@@ -790,6 +793,11 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
         if (L.ld != LD_RGB && img_waves < 1024 &&
             !(key.mt == 8 && waves1 >= 512 && (L.dt != DT_FP8 || L.tag == LIC_GA2)))
             key.ksplit = 4;
+        if (L.ld == LD_RGB && a.ws && L.nphase == 1 && a.kk == 5 && a.s_in == 2 && a.Wg % 32 == 0 &&
+            image_available(L.cop, key.dt == DT_F32 ? DT_F32X : key.dt)) {
+            if (key.dt == DT_F32) key.dt = DT_F32X;
+            image = true;
+        }
         if (L.ld != LD_RGB && key.ksplit == 1 && a.wt) {
             // Both operands staged in LDS, one or two 16-pixel tiles per wave
             // (the same sums either way).
@@ -884,12 +892,12 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
     const long nblocks = tiles * L.nphase * a.ncog;
     if (nblocks <= 0 && !chosen) return LIC_OK;
     if (nblocks > (1L << 30)) { *errp = "launch too large"; return LIC_E_BUDGET; }
-    if (!staged && !rgb && !sk.mt && !kernel_available(key)) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
+    if (!staged && !rgb && !image && !sk.mt && !kernel_available(key)) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
     if (chosen) {
         *chosen = key;
         return LIC_OK;
     }
-    hipError_t e = rgb ? launch_rgb(L.cin, L.dt, a, s) : staged ? launch_gdn(key, a, (int)nblocks, s)
+    hipError_t e = image ? launch_image(key.dt, a, s) : rgb ? launch_rgb(L.cin, L.dt, a, s) : staged ? launch_gdn(key, a, (int)nblocks, s)
                    : sk.mt ? launch_split(sk, a, (int)nblocks, s) : launch_conv(key, a, (int)nblocks, s);
     if (e != hipSuccess) {
         *errp = std::string("kernel launch failed: ") + hipGetErrorString(e);
