@@ -94,6 +94,7 @@ struct ConvArgs {
                              // (inverse y = x n); 0 = GDN, n = beta + gamma (x*x), y = x / sqrt(n)
     int Hc, Wc;              // EP_RGB crop size
     int kk, pad;             // LD_RGB kernel size and padding
+    int tw;                  // window kernels: columns of a block's pixel tile (16 or 32)
     const float* rscale;     // DT_FP8: per packed row, weight scale x input scale
     float out_q;             // DT_FP8: activations are stored as e4m3(out_q * value)
     int out_e4m3;            // DT_BF16 kernels: store e4m3(out_q * value) instead of bf16

@@ -33,13 +33,12 @@
 
 #include "../../include/lic.h"
 #include "conv_args.h"
+#include "gdn_finish.h"
 #include "kernels.h"
 #include "lds_stage.h"
 #include "mfma_common.h"
 
 namespace lic {
-
-template <int I> using Int = std::integral_constant<int, I>;
 
 // WAVES: 4 with two blocks per CU, or 8 with one where two blocks' stages do
 // not fit its 160 KB of LDS (either way two waves per SIMD, 256 registers).
@@ -61,17 +60,10 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
     constexpr int L = AW + NB;                                     // loads per wave and chunk
     static_assert(RB == 32 || RB == 64 || RB == 128, "whole pieces per pixel");
     constexpr int STW = (AP + WAVES * NB) * 256;                   // words per stage
-    constexpr int GP = DT == DT_F32X ? 3 : 2;                      // bf16 parts of gamma and x*x
-    constexpr int NPAIR = MT / 2;
-    constexpr int GSW = MT * GP * 256;                             // words per 32-channel gamma slice
-    constexpr int OROWMAX = MT * 16 + 4;                           // words per staged output pixel (float)
-    constexpr int OUTW = WAVES * 16 * (DT == DT_F32X ? OROWMAX : MT * 8 + 4);
     constexpr int MUW = LD == LD_I8 ? CIN : 0;                     // the symbols' offsets, behind the stages
+    constexpr int OUTW = gdn_out_words(MT, WAVES, DT);
     constexpr int SMW = ST * STW + MUW > OUTW ? ST * STW + MUW : OUTW;
     static_assert(SMW * 4 <= (WAVES == 4 ? 81920 : 163840), "two waves per SIMD");
-    constexpr int GSL = SMW / GSW < NPAIR ? SMW / GSW : NPAIR;     // gamma slices in LDS at once
-    static_assert(GSL >= 2, "gamma ring");
-    constexpr int GW = (MT * GP + WAVES - 1) / WAVES;              // loads of a slice per wave
     __shared__ __attribute__((aligned(16))) uint32_t smem[SMW];
 
     const int lane = threadIdx.x & 63;
@@ -295,160 +287,14 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
     }
     lds_barrier();                                      // every stage is free
 
-    // ------------------------------------------------------------ GDN
-    // n = beta + gamma (x*x) as in conv_igemm: x*x and gamma in GP bf16 parts,
-    // 32 channels per K chunk; gamma slice p = [mt][part][lane][8]
-    const Buf gbuf = make_buf(a.gt);
-    auto g_issue = [&](int p) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < GW; ++u) {
-            const int f = MT * GP % WAVES == 0 ? wave * GW + u : min(wave * GW + u, MT * GP - 1);
-            buf_load_lds(gbuf, smem + (p % GSL) * GSW + f * 256, lane * 16, (p * (MT * GP) + f) * 1024);
-        }
-    };
-    if constexpr (DT == DT_FP8) {
-        // undo the operand scales, then add the bias
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const f4 rs = *reinterpret_cast<const f4*>(a.rscale + mt * 16 + kg * 4);
-            const f4 b = *reinterpret_cast<const f4*>(a.bias + mt * 16 + kg * 4);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = acc[mt][nt] * rs + b;
-        }
-    }
-    f4 nacc[MT][NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const f4 b = *reinterpret_cast<const f4*>(a.beta + mt * 16 + kg * 4);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) nacc[mt][nt] = b;
-    }
-#pragma unroll
-    for (int p = 0; p < GSL; ++p) g_issue(p);
-    auto pair = [&](auto pc_) __attribute__((always_inline)) {
-        constexpr int p = decltype(pc_)::value;
-        bf16x8 S[GP][NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            float r[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float x = acc[2 * p + i / 4][nt][i % 4];
-                r[i] = a.norm1 ? fabsf(x) : x * x;
-            }
-            bf16x8 parts[GP];
-            split_parts<GP>(r, parts);
-#pragma unroll
-            for (int g = 0; g < GP; ++g) S[g][nt] = parts[g];
-        }
-        // slices issued so far: GSL at first, then one more per step from step 1 on
-        constexpr int issued = p == 0 ? GSL : (GSL + p - 1 < NPAIR ? GSL + p - 1 : NPAIR);
-        wait_vm<(issued - 1 - p) * GW>();
-        lds_barrier();
-        if constexpr (p >= 1 && p - 1 + GSL < NPAIR) g_issue(p - 1 + GSL);
-        const uint32_t* gs = smem + (p % GSL) * GSW + lane * 4;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            bf16x8 G[GP];
-#pragma unroll
-            for (int g = 0; g < GP; ++g)
-                G[g] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(gs + (mt * GP + g) * 256));
-            auto mul = [&](int g, int s) __attribute__((always_inline)) {
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    nacc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(G[g], S[s][nt], nacc[mt][nt], 0, 0, 0);
-            };
-            if constexpr (GP == 3) {
-                mul(0, 2);
-                mul(1, 1);
-                mul(2, 0);
-            }
-            mul(0, 1);
-            mul(1, 0);
-            mul(0, 0);
-        }
-    };
-    auto pairs = [&](auto... p) __attribute__((always_inline)) { (pair(p), ...); };
-    static_assert(NPAIR == 4 || NPAIR == 6, "128 or 192 channels");
-    pairs(Int<0>{}, Int<1>{}, Int<2>{}, Int<3>{});
-    if constexpr (NPAIR == 6) pairs(Int<4>{}, Int<5>{});
-    lds_barrier();                                      // the last slice has been read
-
-    // ------------------------------------------------------------ output
-    // y = x / sqrt(n) (inverse: x sqrt(n)); 1DN: x / n (x n).  Each wave
-    // writes its pixels' channels to LDS rows and then to memory in 16-byte
-    // pieces, consecutive lanes on one pixel; the 16 bytes of padding per row
-    // (which spread the rows over the banks) hold the pixel's output offset.
-    auto emit = [&](auto oec) __attribute__((always_inline)) {
-        constexpr int OE = decltype(oec)::value;        // bytes per stored value
-        constexpr int OROW = MT * 16 * OE / 4 + 4;      // words per row
-        uint32_t* const ob = smem + wave * (16 * OROW);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int p = pix0 + nt * 16 + l16;
-            const bool pv = p < total;
-            const int q = pv ? p : 0;
-            const int im = q / HWg, r = q - im * HWg;
-            const int y = r / a.Wg, x = r - y * a.Wg;
-            uint32_t* const row = ob + l16 * OROW;
-            if (kg == 0) {
-                const long o = pv ? (((long)im * a.Hout + y * a.s_out + ph->oy) * a.Wout + x * a.s_out + ph->ox) *
-                                        (a.co_ld ? a.co_ld : a.Co) + a.co_off
-                                  : -1L;
-                *reinterpret_cast<long*>(row + MT * 16 * OE / 4) = o;
-            }
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                f4 v;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float nv = nacc[mt][nt][i];
-                    if (EP == EP_GDN)
-                        v[i] = acc[mt][nt][i] * (a.norm1 ? __builtin_amdgcn_rcpf(nv) : __builtin_amdgcn_rsqf(nv));
-                    else
-                        v[i] = acc[mt][nt][i] * (a.norm1 ? nv : __builtin_amdgcn_sqrtf(nv));
-                }
-                if constexpr (OE == 4) {
-                    *reinterpret_cast<f4*>(row + mt * 16 + kg * 4) = v;
-                } else if constexpr (OE == 2) {
-                    bf16x4 h;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) h[i] = (__bf16)v[i];
-                    *reinterpret_cast<bf16x4*>(row + mt * 8 + kg * 2) = h;
-                } else {
-                    const f4 w = a.out_q * v;
-                    if (a.sat) {
-                        const bool s = pv && (fabsf(w[0]) > 448.0f || fabsf(w[1]) > 448.0f || fabsf(w[2]) > 448.0f ||
-                                              fabsf(w[3]) > 448.0f);
-                        const unsigned long long m = __ballot(s);
-                        if (m && lane == __ffsll((long long)m) - 1) atomicAdd(a.sat, (unsigned long long)__popcll(m));
-                    }
-                    row[mt * 4 + kg] = e4m3x2(w[0], w[1]) | (e4m3x2(w[2], w[3]) << 16);
-                }
-            }
-            wave_order();
-            constexpr int PPR = MT * OE;                // 16-byte pieces per pixel
-            static_assert(16 * PPR % 64 == 0, "whole stores");
-#pragma unroll
-            for (int j = 0; j < 16 * PPR / 64; ++j) {
-                const int q2 = j * 64 + lane, p2 = q2 / PPR, c = q2 - (q2 / PPR) * PPR;
-                const uint32_t* orow = ob + p2 * OROW;
-                const long o = *reinterpret_cast<const long*>(orow + MT * 16 * OE / 4);
-                const u32x4 v = *reinterpret_cast<const u32x4*>(orow + c * 4);
-                if (o >= 0) *reinterpret_cast<u32x4*>(static_cast<uint8_t*>(a.out) + o * OE + c * 16) = v;
-            }
-            wave_order();
-        }
-    };
-    if constexpr (DT == DT_F32X) {
-        emit(std::integral_constant<int, 4>{});
-    } else if constexpr (DT == DT_BF16) {
-        if (a.out_e4m3) emit(std::integral_constant<int, 1>{});
-        else emit(std::integral_constant<int, 2>{});
-    } else {
-        if (a.out_bf16) emit(std::integral_constant<int, 2>{});
-        else emit(std::integral_constant<int, 1>{});
-    }
+    const long oc = a.co_ld ? a.co_ld : a.Co;
+    gdn_finish<MT, NT, NT, WAVES, SMW, EP, DT, false>(a, nullptr, acc, smem, lane, wave, [&](int nt) __attribute__((always_inline)) {
+        const int p = pix0 + nt * 16 + l16;
+        const int q = p < total ? p : 0;
+        const int im = q / HWg, r = q - im * HWg;
+        const int y = r / a.Wg, x = r - y * a.Wg;
+        return p < total ? (((long)im * a.Hout + y * a.s_out + ph->oy) * a.Wout + x * a.s_out + ph->ox) * oc + a.co_off : -1L;
+    });
 }
 
 // ---------------------------------------------------------------- registry

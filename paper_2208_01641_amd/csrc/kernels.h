@@ -42,6 +42,11 @@ hipError_t launch_rgb(int cin, int dt, const ConvArgs& args, hipStream_t stream)
 // of whole 32-pixel tiles
 bool image_available(int cop, int dt);
 hipError_t launch_image(int dt, const ConvArgs& args, hipStream_t stream);
+// IGDN layers with the pixels of a tile and its halo in LDS (window_kernels.hip):
+// every tap within one pixel; a.tw set
+constexpr int kWindowPixels = 256;
+bool window_available(int tag, int cin, int cop, int dt);
+hipError_t launch_window(int tag, int cin, int cop, int dt, const ConvArgs& args, hipStream_t stream);
 hipError_t launch_conv(const KernelKey& k, const ConvArgs& args, int nblocks, hipStream_t stream);
 
 // Context model, element-wise steps of the two checkerboard passes (layout

@@ -22,12 +22,14 @@ template <int N> __device__ __forceinline__ void wait_vm_lds()
 }
 
 // workgroup barrier that orders LDS accesses only: loads into LDS that are
-// still in flight are waited for by wait_vm where their stage is used
+// still in flight are waited for by wait_vm where their stage is used (a
+// workgroup fence makes the compiler wait for all of them)
 __device__ __forceinline__ void lds_barrier()
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);                 // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    asm volatile("" ::: "memory");
 }
 
 // orders one wave's LDS accesses before and after (lanes read each other's)

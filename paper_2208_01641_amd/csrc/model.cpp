@@ -777,7 +777,7 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
 {
     KernelKey key{L.tag, L.cin, 0, 0, 0, 1, L.ld, L.ep, L.dt};
     const long pixels = (long)a.n * a.Hg * a.Wg;
-    bool staged = false, rgb = false, image = false;
+    bool staged = false, rgb = false, image = false, window = false;
     if (L.ep == EP_GDN || L.ep == EP_IGDN) {
         key.mt = L.cop / 16;
         key.nt = key.mt <= 8 ? 2 : 1;
@@ -809,6 +809,25 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
             if (gdn_available(ks)) {
                 key = ks;
                 staged = true;
+            }
+            // Large grids of g_s: a tile's pixels and their halo in LDS (again the
+            // same sums), 256 pixels and a phase per block.  16 x 16 or 8 x 32 pixels, whichever
+            // leaves fewer tiles.  Measured against the above (us; blocks in
+            // brackets): bf16 30 -> 33 [240], 52 -> 42 [416], 53 -> 43 [448], 104 -> 77
+            // [960]; FP32 86 -> 91 [240], 160 -> 138 [416], 350 -> 297 [960]; e4m3 22
+            // -> 23 [240], 38 -> 31 [416], 77 -> 56 [960]; 192 channels bf16 54 -> 55
+            // [240], 101 -> 87 [448], e4m3 41 -> 36 [240], 74 -> 59 [448].  Just above
+            // 512 blocks, where those kernels just fill the chip twice, they stay
+            // ahead (FP32 176 against 183, e4m3 43 against 46 [540]).
+            if (staged && L.halo1 && L.ep == EP_IGDN && L.ld == LD_F32 && window_available(L.tag, L.cin, L.cop, key.dt)) {
+                auto blocks = [&](int tw) {
+                    const int th = kWindowPixels / tw;
+                    return (long)a.n * ((a.Hg + th - 1) / th) * ((a.Wg + tw - 1) / tw) * L.nphase;
+                };
+                a.tw = blocks(32) < blocks(16) ? 32 : 16;
+                const long nb = blocks(a.tw);
+                const bool twice = nb > 512 && (pixels + 127) / 128 * L.nphase <= 1024;
+                window = nb >= (L.cop == 192 && key.dt == DT_FP8 ? 200 : 400) && !twice;
             }
         }
     } else if (L.ep == EP_RGB) {
@@ -897,7 +916,7 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
         *chosen = key;
         return LIC_OK;
     }
-    hipError_t e = image ? launch_image(key.dt, a, s) : rgb ? launch_rgb(L.cin, L.dt, a, s) : staged ? launch_gdn(key, a, (int)nblocks, s)
+    hipError_t e = window ? launch_window(L.tag, L.cin, L.cop, key.dt, a, s) : image ? launch_image(key.dt, a, s) : rgb ? launch_rgb(L.cin, L.dt, a, s) : staged ? launch_gdn(key, a, (int)nblocks, s)
                    : sk.mt ? launch_split(sk, a, (int)nblocks, s) : launch_conv(key, a, (int)nblocks, s);
     if (e != hipSuccess) {
         *errp = std::string("kernel launch failed: ") + hipGetErrorString(e);
