@@ -165,7 +165,7 @@ PackMap pack_map_checkerboard(int ci, int co, int k, int part, bool pair_rows)
     return m;
 }
 
-TileOrder tile_order(const PackMap& m, int dt)
+TileOrder tile_order(const PackMap& m, int dt, bool quads)
 {
     TileOrder o;
     const int kch = dt == DT_F32 ? 16 : dt == DT_FP8 ? 128 : 32;
@@ -187,7 +187,7 @@ TileOrder tile_order(const PackMap& m, int dt)
                                 c = x % m.cin;
                             } else {
                                 t = k % ntaps;
-                                c = (k / ntaps) * kch + (l / 16) * ke + e;
+                                c = (k / ntaps) * kch + (quads ? (e / 4) * 16 + (l / 16) * 4 + e % 4 : (l / 16) * ke + e);
                             }
                             const size_t j = m.off[f] + ((size_t)t * m.cop + mt * 16 + l % 16) * m.cin + c;
                             o.idx.push_back(t < ntaps ? (int32_t)j : -1);

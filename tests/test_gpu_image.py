@@ -68,3 +68,30 @@ def test_image_layers(prec, N, M, n, H, W):
     c.run_layer("GS3", n, H, W, y, img)
     assert torch.equal(img, pre[:, :, :H, :W].clamp(0.0, 1.0))
     c.close()
+
+
+@pytest.mark.parametrize("n,H,W", SIZES)
+@pytest.mark.parametrize("N,M", [(128, 192), (192, 320)])
+def test_output_layer_fp32_error(N, M, n, H, W):
+    """g_s's FP32 output layer (split operands) against float64, in the 2-norm: each
+    of up to 54 sums rounds once more (2^-24 sqrt(54) = 4.4e-7, twice that for what
+    partial sums exceed the result by); one order of part products left out
+    would give 2^-17 = 7.6e-6."""
+    import torch
+
+    from paper_2208_01641_amd import Codec
+    P = synth.model_params(1, N, M, gamma="dense")
+    d = dims(H, W)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(H + W + n)
+    x = torch.randn((n, d["Hp"] // 2, d["Wp"] // 2, N), device="cuda", generator=g)
+    img = torch.empty((n, 3, H, W), device="cuda")
+    pre = torch.empty((n, 3, d["Hp"], d["Wp"]), device="cuda")
+    c = Codec(synth.weight_blob(P, 1, N, M), kind=1, N=N, M=M, max_h=64, max_w=64, max_in_flight=1)
+    c.run_layer("GS3", n, H, W, x, img, pre)
+    w, b = (torch.from_numpy(np.asarray(P["gs3" + k], np.float64)).cuda() for k in (".w", ".b"))
+    ref = deconv64(torch, x.double(), w, b).permute(0, 3, 1, 2)
+    err = float((pre.double() - ref).norm() / ref.norm())
+    assert err < 1e-6, f"{err:.2e}"
+    assert torch.equal(img, pre[:, :, :H, :W].clamp(0.0, 1.0))
+    c.close()
