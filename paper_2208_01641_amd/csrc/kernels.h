@@ -35,6 +35,8 @@ struct SplitKey {
 };
 bool split_available(const SplitKey& k);
 hipError_t launch_split(const SplitKey& k, const ConvArgs& args, int nblocks, hipStream_t stream);
+// GDN / IGDN of FP32 activations [pixel][cop] in place (128 or 192 channels)
+hipError_t launch_gdn_apply(int cop, int ep, const ConvArgs& args, hipStream_t stream);
 // g_s's output layer (rgb_kernels.hip): 3 x 3 neighbourhood, grid a multiple of 8 x 32
 bool rgb_available(int cin, int dt);
 hipError_t launch_rgb(int cin, int dt, const ConvArgs& args, hipStream_t stream);

@@ -886,6 +886,7 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
     // [240], 16 x 16 15 [480]; its third 31, 18, 12 [60], 10 [120]; bf16 g_a's
     // last 18 [360], 21 [720].
     SplitKey sk{};
+    bool two_pass = false;
     if (key.ksplit > 1 && a.ws) {
         const bool gdn = L.ep == EP_GDN || L.ep == EP_IGDN;
         sk = SplitKey{4, 1, gdn ? key.mt / 4 : 1, key.ksplit, L.ld, L.ep, L.dt};
@@ -900,7 +901,22 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
         } else if (L.cop % 64 != 0 || blocks(4, 1) < 448) {
             sk.mt = L.cop % 32 == 0 && (blocks(2, 1) >= 200 || key.ksplit != 8) ? 2 : 1;
         }
-        if (split_available(sk)) a.ncog = gdn ? 1 : L.cop / (16 * sk.mt);
+        // The smallest FP32 GDN layers leave most of the chip idle in blocks of
+        // all rows: the sums in blocks of 16 or 32 rows instead, then the normalisation in
+        // place by a second launch (layer call, us; blocks of all rows in
+        // brackets): GA2 49 -> 31 [4], 49 -> 31 [16], 49 -> 36 [64], 50 -> 42 [96], 52 ->
+        // 51 [140]; GS1 33 -> 29 [64], 33 -> 34 [144]; 192 channels GA1 83 -> 51 [64], 88 ->
+        // 76 [144], 95 -> 106 [256].  Blocks of 16 rows up to 48: 31 against 35 [16], 37
+        // against 36 [64].
+        const long whole = gdn ? blocks(4, 1) : 0;
+        if (gdn && L.dt == DT_F32 && !a.co_ld && whole <= (L.cop == 128 ? 128 : 160)) {
+            const SplitKey sums{whole <= 48 ? 1 : 2, 1, 1, key.ksplit, L.ld, EP_NONE, DT_F32};
+            if ((L.cop == 128 || L.cop == 192) && split_available(sums)) {
+                sk = sums;
+                two_pass = true;
+            }
+        }
+        if (split_available(sk)) a.ncog = gdn && !two_pass ? 1 : L.cop / (16 * sk.mt);
         else sk = SplitKey{};
     }
     const long per_block = (long)(key.waves / key.ksplit) * key.nt * 16;
@@ -919,6 +935,7 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
     }
     hipError_t e = window ? launch_window(L.tag, L.cin, L.cop, key.dt, a, s) : image ? launch_image(key.dt, a, s) : rgb ? launch_rgb(L.cin, L.dt, a, s) : staged ? launch_gdn(key, a, (int)nblocks, s)
                    : sk.mt ? launch_split(sk, a, (int)nblocks, s) : launch_conv(key, a, (int)nblocks, s);
+    if (e == hipSuccess && two_pass) e = launch_gdn_apply(L.cop, L.ep, a, s);
     if (e != hipSuccess) {
         *errp = std::string("kernel launch failed: ") + hipGetErrorString(e);
         return LIC_E_HIP;

@@ -45,6 +45,68 @@
 
 namespace lic {
 
+// n = beta + gamma (x*x) (1DN: |x|) as in gdn_finish.h, spread over the waves of a
+// block: wave w has row block w of every pixel tile (x), and gamma's fragments
+// of those rows (G).  The squares' bf16 parts go to LDS as fragments
+// [nt][p][part][lane][8]: row block 2p + h fills half h.
+template <int TB, int NT, int GP, int EP>
+__device__ __forceinline__ void spread_gdn(const ConvArgs& a, const f4 (&x)[NT], const u32x4 (&G)[TB / 2][GP], uint32_t* S, int lane,
+                                           int wave, f4 (&y)[NT])
+{
+    constexpr int NPAIR = TB / 2;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        f4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = a.norm1 ? fabsf(x[nt][i]) : x[nt][i] * x[nt][i];
+#pragma unroll
+        for (int g = 0; g < GP; ++g) {
+            bf16x4 h;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                h[i] = (__bf16)r[i];
+                r[i] -= (float)h[i];
+            }
+            *reinterpret_cast<bf16x4*>(S + ((nt * NPAIR + (wave >> 1)) * GP + g) * 256 + lane * 4 + (wave & 1) * 2) = h;
+        }
+    }
+    f4 nacc[NT];
+    const f4 be = *reinterpret_cast<const f4*>(a.beta + wave * 16 + (lane >> 4) * 4);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) nacc[nt] = be;
+    lds_barrier();
+#pragma unroll
+    for (int p = 0; p < NPAIR; ++p)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            bf16x8 s[GP];
+#pragma unroll
+            for (int g = 0; g < GP; ++g)
+                s[g] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(S + ((nt * NPAIR + p) * GP + g) * 256 + lane * 4));
+            auto mul = [&](int g, int h) __attribute__((always_inline)) {
+                nacc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, G[p][g]), s[h], nacc[nt], 0, 0, 0);
+            };
+            if constexpr (GP == 3) {
+                mul(0, 2);
+                mul(1, 1);
+                mul(2, 0);
+            }
+            mul(0, 1);
+            mul(1, 0);
+            mul(0, 0);
+        }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float nv = nacc[nt][i];
+            if (EP == EP_GDN)
+                y[nt][i] = x[nt][i] * (a.norm1 ? __builtin_amdgcn_rcpf(nv) : __builtin_amdgcn_rsqf(nv));
+            else
+                y[nt][i] = x[nt][i] * (a.norm1 ? nv : __builtin_amdgcn_sqrtf(nv));
+        }
+}
+
 // MT x NT: 16-row and 16-pixel tiles per wave; RG: row groups per block (GDN:
 // RG MT 16 = all channels); KS: K slots; P: chunks in flight per wave; WPS:
 // waves per SIMD the registers are bounded for.
@@ -404,68 +466,15 @@ __global__ void __launch_bounds__(64 * RG * KS, WPS) conv_split(ConvArgs a)
     };
 
     if constexpr (kGdn) {
-        // n = beta + gamma (x*x) (1DN: |x|) as in gdn_kernels.hip; wave w has
-        // row block w of every pixel tile.  The squares' bf16 parts go to LDS
-        // as fragments [nt][p][part][lane][8]: row block 2p + h fills half h.
         f4 x[NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) x[nt] = summed(wave, nt);
         lds_barrier();                                  // the partial sums have been read
-        uint32_t* const S = smem;
+        f4 y[NT];
+        spread_gdn<TB, NT, GP, EP>(a, x, G, smem, lane, wave, y);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            f4 r;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] = a.norm1 ? fabsf(x[nt][i]) : x[nt][i] * x[nt][i];
-#pragma unroll
-            for (int g = 0; g < GP; ++g) {
-                bf16x4 h;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    h[i] = (__bf16)r[i];
-                    r[i] -= (float)h[i];
-                }
-                *reinterpret_cast<bf16x4*>(S + ((nt * NPAIR + (wave >> 1)) * GP + g) * 256 + lane * 4 + (wave & 1) * 2) = h;
-            }
-        }
-        f4 nacc[NT];
-        const f4 be = *reinterpret_cast<const f4*>(a.beta + wave * 16 + kg * 4);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) nacc[nt] = be;
-        lds_barrier();
-#pragma unroll
-        for (int p = 0; p < NPAIR; ++p)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                bf16x8 s[GP];
-#pragma unroll
-                for (int g = 0; g < GP; ++g)
-                    s[g] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(S + ((nt * NPAIR + p) * GP + g) * 256 + lane * 4));
-                auto mul = [&](int g, int h) __attribute__((always_inline)) {
-                    nacc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, G[p][g]), s[h], nacc[nt], 0, 0, 0);
-                };
-                if constexpr (GP == 3) {
-                    mul(0, 2);
-                    mul(1, 1);
-                    mul(2, 0);
-                }
-                mul(0, 1);
-                mul(1, 0);
-                mul(0, 0);
-            }
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            f4 y;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float nv = nacc[nt][i];
-                if (EP == EP_GDN)
-                    y[i] = x[nt][i] * (a.norm1 ? __builtin_amdgcn_rcpf(nv) : __builtin_amdgcn_rsqf(nv));
-                else
-                    y[i] = x[nt][i] * (a.norm1 ? nv : __builtin_amdgcn_sqrtf(nv));
-            }
-            if (fv[nt]) store_act(out_pix(nt) * ldo + a.co_off + wave * 16 + kg * 4, y);
-        }
+        for (int nt = 0; nt < NT; ++nt)
+            if (fv[nt]) store_act(out_pix(nt) * ldo + a.co_off + wave * 16 + kg * 4, y[nt]);
     } else if constexpr (EP == EP_NONE || EP == EP_RELU) {
 #pragma unroll
         for (int t = 0; t < (TILES + W - 1) / W; ++t) {
@@ -575,6 +584,44 @@ __global__ void __launch_bounds__(64 * RG * KS, WPS) conv_split(ConvArgs a)
     }
 }
 
+// The normalisation alone, in place on FP32 activations [pixel][16 TB]: the second
+// pass of the smallest GDN layers, whose sums a plain split-K kernel has left
+// there.  A block of TB waves takes 16 pixels.  What bounds one small layer is the
+// chain of a block's own K loop: with 16 rows a block instead of all, a wave's
+// chunk is 4 FP32 products instead of 16, on 8 (12) times the CUs.  128 x 128 frame,
+// kernel time of both passes against one (us): g_a's second layer 33 -> 19, its
+// third 32 -> 14, g_s's first 27 -> 14.
+template <int TB, int EP>
+__global__ void __launch_bounds__(64 * TB) gdn_apply(ConvArgs a)
+{
+    constexpr int GP = 3, NPAIR = TB / 2;
+    __shared__ __attribute__((aligned(16))) uint32_t S[NPAIR * GP * 256];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int total = a.n * a.Hout * a.Wout, p = blockIdx.x * 16 + (lane & 15);
+    float* const px = static_cast<float*>(a.out) + (long)(p < total ? p : 0) * (16 * TB) + wave * 16 + (lane >> 4) * 4;
+    const u32x4* gt = static_cast<const u32x4*>(a.gt);
+    f4 x[1], y[1];
+    x[0] = *reinterpret_cast<const f4*>(px);
+    u32x4 G[NPAIR][GP];
+#pragma unroll
+    for (int q = 0; q < NPAIR; ++q)
+#pragma unroll
+        for (int g = 0; g < GP; ++g) G[q][g] = gt[((size_t)(q * TB + wave) * GP + g) * 64 + lane];
+    spread_gdn<TB, 1, GP, EP>(a, x, G, S, lane, wave, y);
+    if (p < total) *reinterpret_cast<f4*>(px) = y[0];
+}
+
+hipError_t launch_gdn_apply(int cop, int ep, const ConvArgs& a, hipStream_t stream)
+{
+    const dim3 grid((unsigned)(((long)a.n * a.Hout * a.Wout + 15) / 16));
+    if (cop == 128)
+        hipLaunchKernelGGL((ep == EP_GDN ? gdn_apply<8, EP_GDN> : gdn_apply<8, EP_IGDN>), grid, dim3(512), 0, stream, a);
+    else
+        hipLaunchKernelGGL((ep == EP_GDN ? gdn_apply<12, EP_GDN> : gdn_apply<12, EP_IGDN>), grid, dim3(768), 0, stream, a);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- registry
 struct SplitEntry {
     SplitKey key;
@@ -600,7 +647,11 @@ struct SplitEntry {
 #define LIC_SGF(LD, EP, DT)                                                                                   \
     LIC_S(4, 1, 2, 4, 2, 2, LD, EP, DT), LIC_S(4, 2, 2, 4, 2, 2, LD, EP, DT), LIC_S(4, 1, 3, 4, 2, 3, LD, EP, DT)
 
+// the sums of the smallest GDN layers (a second pass normalises)
+#define LIC_SS(LD) LIC_S(1, 1, 1, 4, 8, 4, LD, EP_NONE, DT_F32)
+
 static const SplitEntry kSplit[] = {
+    LIC_SS(LD_F32), LIC_SS(LD_I8), LIC_S(2, 1, 1, 4, 4, 4, LD_I8, EP_NONE, DT_F32),
     LIC_SE(LD_F32, EP_RELU, DT_F32),  LIC_SE(LD_F32_ABS, EP_RELU, DT_F32), LIC_SE(LD_I8, EP_RELU, DT_F32),
     LIC_SE(LD_F32, EP_QUANT, DT_F32), LIC_SE(LD_F32, EP_QUANT, DT_BF16),   LIC_SEF(LD_F32, EP_QUANT, DT_FP8),
     LIC_SE(LD_F32, EP_INDEX, DT_F32), LIC_SE(LD_F32, EP_NONE, DT_F32),     LIC_SE(LD_F32, EP_MSCALE, DT_F32),

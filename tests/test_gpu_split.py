@@ -120,3 +120,36 @@ def test_split_layer(prec, layer, N, M, n, H, W):
         mu = c.medians() if layer == "HA2" else np.float32(0)
         assert np.array_equal(ints.cpu().numpy(), np.clip(np.rint(v - mu), -64, 64).astype(np.int8))
     c.close()
+
+
+# (layer, N, M, images of the batch, H, W, norm): alone the layer takes two passes
+# (sums in blocks of 16 or of 32 rows, then the normalisation), the batch one
+TWO_PASS = [("GA1", 128, 192, 9, 64, 64, 0), ("GA2", 128, 192, 33, 64, 64, 1), ("GA2", 128, 192, 2, 256, 320, 0),
+            ("GS0", 128, 192, 33, 64, 64, 0), ("GS1", 128, 192, 10, 64, 64, 1), ("GS1", 128, 192, 2, 128, 192, 0),
+            ("GS2", 128, 192, 3, 64, 64, 0), ("GA1", 192, 320, 11, 64, 64, 0), ("GA2", 192, 320, 2, 320, 448, 1),
+            ("GS0", 192, 320, 11, 64, 192, 1), ("GS1", 192, 320, 2, 192, 192, 0)]
+
+
+@pytest.mark.parametrize("layer,N,M,n,H,W,norm", TWO_PASS)
+def test_two_pass_gdn_same_bits(layer, N, M, n, H, W, norm):
+    import torch
+
+    from paper_2208_01641_amd import Codec
+    P = synth.model_params(1, N, M, gamma="dense")
+    d = dims(H, W)
+    di, do = SHAPE[layer]
+    ci = M if layer == "GS0" else N
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + n)
+    x = torch.randn((n, d["Hp"] // di, d["Wp"] // di, ci), device="cuda", generator=g)
+    if layer == "GS0":
+        x = (3 * x).round().clamp(-64, 64).to(torch.int8)
+    out = torch.empty((n, d["Hp"] // do, d["Wp"] // do, N), device="cuda")
+    one = torch.empty((1,) + out.shape[1:], device="cuda")
+    c = Codec(synth.weight_blob(P, 1, N, M), kind=1, N=N, M=M, max_h=64, max_w=64, max_in_flight=1, norm=norm)
+    c.run_layer(layer, n, H, W, x, out)
+    assert bool(out.isfinite().all())
+    for i in range(n):
+        c.run_layer(layer, 1, H, W, x[i:i + 1].contiguous(), one)
+        assert torch.equal(out[i], one[0]), f"image {i} of {n} differs"
+    c.close()
