@@ -16,9 +16,13 @@
 //     (a b128 read takes lanes 0-7 with 16-23, 8-15 with 24-31, ... together);
 //   * gamma comes in fragment order too, and the outputs are transposed in LDS
 //     so that each pixel's channels leave in whole 16-byte pieces.
-// All of it goes straight from memory to LDS (global_load_lds_dwordx4) into a
-// ring of ST stages, ST - 1 chunks ahead, with one barrier per chunk and a
-// wait that leaves the later chunks in flight.
+// All of it goes straight from memory to LDS (buffer loads with the lds bit)
+// into a ring of ST stages, ST - 1 chunks ahead, with one barrier per chunk and a
+// wait that leaves the later chunks in flight.  Grids that give a SIMD one
+// wave have nothing to hide a chunk's LDS reads and the splitting of its
+// pixels behind: where a third stage fits, those are done for the next chunk among
+// the products of this one (720p split-FP32 GA2 95 -> 87 us, GS0 59 -> 50; 360p GA1
+// 95 -> 87).
 //
 // The products, their order and the order of the channels and taps are those
 // of conv_igemm, so the results are the same bits.
@@ -57,14 +61,18 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
     constexpr int NB = (NT * 16 + PPI - 1) / PPI;                  // pixel loads per wave and chunk
     constexpr int AP = MT * SUB;                                   // weight fragments (KB) per chunk
     constexpr int AW = (AP + WAVES - 1) / WAVES;                   // loads of them per wave (past the end: the last again)
-    constexpr int L = AW + NB;                                     // loads per wave and chunk
+    // stages of weights (ST) and of pixels: three of pixels where three of both do
+    // not fit (not e4m3, which has nothing to convert: 40.1 us so, 41.4 with it)
+    constexpr int PS = ST == 2 && DT == DT_F32X && NT == 1 ? 3 : ST;
     static_assert(RB == 32 || RB == 64 || RB == 128, "whole pieces per pixel");
-    constexpr int STW = (AP + WAVES * NB) * 256;                   // words per stage
+    constexpr int STW = AP * 256, PSW = WAVES * NB * 256;           // words per stage
+    constexpr int RINGW = ST * STW + PS * PSW;
     constexpr int MUW = LD == LD_I8 ? CIN : 0;                     // the symbols' offsets, behind the stages
     constexpr int OUTW = gdn_out_words(MT, WAVES, DT);
-    constexpr int SMW = ST * STW + MUW > OUTW ? ST * STW + MUW : OUTW;
+    constexpr int SMW = RINGW + MUW > OUTW ? RINGW + MUW : OUTW;
     static_assert(SMW * 4 <= (WAVES == 4 ? 81920 : 163840), "two waves per SIMD");
     __shared__ __attribute__((aligned(16))) uint32_t smem[SMW];
+    uint32_t* const pring = smem + ST * STW;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -108,7 +116,7 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
 
     constexpr int KC = DT == DT_FP8 ? 1 : CIN / KCH;
     const int nk = DT == DT_FP8 ? (ntaps * CIN + KCH - 1) / KCH : ntaps * KC;
-    int i_t = 0, i_s = 0, i_k = 0, i_st = 0;             // next chunk to load: tap, channel slice, index, stage
+    int i_t = 0, i_s = 0, i_k = 0, i_st = 0, w_k = 0, w_st = 0;    // next chunk to load: tap, channel slice, index, stage; weights
     const int toffv = ((int)(short)(tapv & 0xffff) * a.Win + (tapv >> 16)) * (CIN * ESZ);   // bytes to tap t
     auto tap_off = [&](int t) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(toffv, t < ntaps ? t : 0); };
     auto tap = [&](int t, int& dy, int& dx) __attribute__((always_inline)) {
@@ -116,16 +124,20 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
         dy = t < ntaps ? (int)(short)(tv & 0xffff) : -(1 << 20);
         dx = tv >> 16;
     };
-    auto issue = [&]() __attribute__((always_inline)) {
-        uint32_t* const st = smem + i_st * STW;
+    auto issue_w = [&]() __attribute__((always_inline)) {
+        uint32_t* const st = smem + w_st * STW;
 #pragma unroll
         for (int u = 0; u < AW; ++u) {
             const int f = AP % WAVES == 0 ? wave * AW + u : min(wave * AW + u, AP - 1);
-            buf_load_lds(wbuf, st + f * 256, lane * 16, (i_k * AP + f) * 1024);
+            buf_load_lds(wbuf, st + f * 256, lane * 16, (w_k * AP + f) * 1024);
         }
+        ++w_k;
+        if (++w_st == ST) w_st = 0;
+    };
+    auto issue_p = [&]() __attribute__((always_inline)) {
         // a chunk's window is the buffer's base moved by its tap; lanes whose
         // tap is out of the image read zero
-        uint32_t* const sb = st + (AP + wave * NB) * 256;
+        uint32_t* const sb = pring + i_st * PSW + wave * NB * 256;
         if constexpr (DT == DT_FP8) {
             const int f0 = i_k * KCH, tA = f0 / CIN, c0 = f0 - tA * CIN;
             const int step = CIN % KCH != 0 ? tap_off(tA + 1) - CIN - tap_off(tA) : 0;
@@ -145,13 +157,13 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
             ++i_s;
         }
         ++i_k;
-        if (++i_st == ST) i_st = 0;
+        if (++i_st == PS) i_st = 0;
     };
 
     // symbols: the offsets in LDS, and the pixels of this lane's fragments
     // (an out-of-image tap reads symbol 0 and must not add the offset)
-    float* const mus = reinterpret_cast<float*>(smem + ST * STW);
-    int fy[NT], fx[NT], c_t = 0, c_s = 0;
+    float* const mus = reinterpret_cast<float*>(smem + RINGW);
+    int fy[NT], fx[NT], r_t = 0, r_s = 0;
     if constexpr (LD == LD_I8) {
         for (int c = threadIdx.x; c < CIN; c += 64 * WAVES) mus[c] = a.mu_in[c];
 #pragma unroll
@@ -173,72 +185,99 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = b;
     }
 
-    // One chunk: the fragments of stage st are read first (LDS returns them in
-    // order, so the products start on the first while the rest arrive), the
-    // loads of a later chunk are issued in their shadow, then the products.
-    // Split-FP32 holds two of its three-part weight fragments at a time.
+    // With a third stage the next chunk's fragments are read (and the pixels'
+    // split or converted) in the shadow of this one's products, before its
+    // barrier; else they are read first and the loads of a later chunk are
+    // issued in their shadow.
+    constexpr bool BAHEAD = PS >= 3, AAHEAD = ST >= 3;
+    constexpr int PF = DT == DT_F32X ? 2 : 4;                      // weight fragments held
+    static_assert(MT % PF == 0, "fragment slots");
     const int brow = LPR == 2 ? l16 * 8 + kg * 2 : l16 * (RB / 4) + (((LPR == 4 ? kg : 2 * kg) ^ rot(l16)) * 4);
-    constexpr int PF = DT == DT_F32X ? 2 : MT;
-    auto step = [&](const uint32_t* st, auto more) __attribute__((always_inline)) {
-        const uint32_t* bs = st + (AP + wave * NB) * 256 + brow;
-        const uint32_t* bs2 = st + (AP + wave * NB) * 256 + (brow ^ 4);
-        const uint32_t* as = st + lane * 4;
-        u32x4 Bl[NT], Bh[NT], A[MT][SUB];
-        uint2 Bs[NT];
-        f4 mu[2];
-        if constexpr (LD == LD_I8) {
+    struct Pix {                                                   // a pixel fragment as the products take it
+        u32x4 p[DT == DT_BF16 ? 1 : DT == DT_FP8 ? 2 : 3];
+    };
+    u32x4 Bl[NT], Bh[NT], A[PF][SUB];
+    uint2 Bs[NT];
+    f4 mu[2];
+    bool ok[NT];
+    Pix N[NT];
+    int ra_st = 0, rb_st = 0;
+    auto readA = [&](int mt) __attribute__((always_inline)) {
+        const uint32_t* const as = smem + ra_st * STW + lane * 4;
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) Bs[nt] = *reinterpret_cast<const uint2*>(bs + nt * 16 * (RB / 4));
-#pragma unroll
-            for (int e = 0; e < 2; ++e) mu[e] = *reinterpret_cast<const f4*>(mus + c_s * KCH + kg * 8 + e * 4);
-        } else
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            Bl[nt] = *reinterpret_cast<const u32x4*>(bs + nt * 16 * (RB / 4));
-            if constexpr (LPR == 8) Bh[nt] = *reinterpret_cast<const u32x4*>(bs2 + nt * 16 * (RB / 4));
-        }
-        auto readA = [&](int mt) __attribute__((always_inline)) {
-#pragma unroll
-            for (int g = 0; g < SUB; ++g) A[mt][g] = *reinterpret_cast<const u32x4*>(as + (mt * SUB + g) * 256);
-        };
-#pragma unroll
-        for (int mt = 0; mt < PF; ++mt) readA(mt);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (decltype(more)::value) issue();
-        Split3 Bx[NT];
+        for (int g = 0; g < SUB; ++g) A[mt % PF][g] = *reinterpret_cast<const u32x4*>(as + (mt * SUB + g) * 256);
+    };
+    auto readB = [&]() __attribute__((always_inline)) {
+        const uint32_t* const bs = pring + rb_st * PSW + wave * NB * 256;
         if constexpr (LD == LD_I8) {
             int dy, dx;
-            tap(c_t, dy, dx);
+            tap(r_t, dy, dx);
+            const int c = r_s < KC ? r_s * KCH : 0;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) mu[e] = *reinterpret_cast<const f4*>(mus + c + kg * 8 + e * 4);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const bool ok = ((unsigned)(fy[nt] + dy) < (unsigned)a.Hin) & ((unsigned)(fx[nt] + dx) < (unsigned)a.Win);
-                float v[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    v[e] = (float)(int8_t)((e < 4 ? Bs[nt].x : Bs[nt].y) >> (8 * (e % 4))) + (ok ? mu[e / 4][e % 4] : 0.0f);
-                if constexpr (DT == DT_F32X) {
-                    Bx[nt] = split3(v);
-                } else {
-                    bf16x8 h;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) h[e] = (__bf16)v[e];
-                    Bl[nt] = __builtin_bit_cast(u32x4, h);
-                }
+                Bs[nt] = *reinterpret_cast<const uint2*>(bs + brow + nt * 16 * (RB / 4));
+                ok[nt] = ((unsigned)(fy[nt] + dy) < (unsigned)a.Hin) & ((unsigned)(fx[nt] + dx) < (unsigned)a.Win);
             }
-            if (++c_t == ntaps) {
-                c_t = 0;
-                ++c_s;
+            if (++r_t == ntaps) {
+                r_t = 0;
+                ++r_s;
             }
-        } else if constexpr (DT == DT_F32X) {
+        } else {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const f4 lo = __builtin_bit_cast(f4, Bl[nt]), hi = __builtin_bit_cast(f4, Bh[nt]);
-                const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                Bx[nt] = split3(v);
+                Bl[nt] = *reinterpret_cast<const u32x4*>(bs + brow + nt * 16 * (RB / 4));
+                if constexpr (LPR == 8) Bh[nt] = *reinterpret_cast<const u32x4*>(bs + (brow ^ 4) + nt * 16 * (RB / 4));
             }
         }
+        if (++rb_st == PS) rb_st = 0;
+    };
+    auto prepare = [&](int nt) __attribute__((always_inline)) -> Pix {
+        Pix r;
+        if constexpr (LD == LD_F32 && DT != DT_F32X) {
+            r.p[0] = Bl[nt];
+            if constexpr (DT == DT_FP8) r.p[1] = Bh[nt];
+        } else {
+            float v[8];
+            if constexpr (LD == LD_I8) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    v[e] = (float)(int8_t)((e < 4 ? Bs[nt].x : Bs[nt].y) >> (8 * (e % 4))) + (ok[nt] ? mu[e / 4][e % 4] : 0.0f);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = __builtin_bit_cast(f4, e < 4 ? Bl[nt] : Bh[nt])[e % 4];
+            }
+            if constexpr (DT == DT_F32X) {
+                const Split3 x = split3(v);
+#pragma unroll
+                for (int g = 0; g < 3; ++g) r.p[g] = __builtin_bit_cast(u32x4, x.p[g]);
+            } else {
+                bf16x8 h;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) h[e] = (__bf16)v[e];
+                r.p[0] = __builtin_bit_cast(u32x4, h);
+            }
+        }
+        return r;
+    };
+    auto step = [&](auto more) __attribute__((always_inline)) {
+        if constexpr (!BAHEAD) readB();
+        if constexpr (!AAHEAD) {
+#pragma unroll
+            for (int mt = 0; mt < PF; ++mt) readA(mt);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(more)::value) {
+            issue_w();
+            issue_p();
+        }
+        Pix C[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) C[nt] = BAHEAD ? N[nt] : prepare(nt);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
+            const u32x4(&W)[SUB] = A[mt % PF];
             if constexpr (DT == DT_F32X) {
                 // the six part products, smallest first
                 constexpr int pa[6] = {0, 1, 2, 0, 1, 0}, pbx[6] = {2, 1, 0, 1, 0, 0};
@@ -246,15 +285,13 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
                 for (int s = 0; s < 6; ++s)
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt)
-                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[mt][pa[s]]),
-                                                                              Bx[nt].p[pbx[s]], acc[mt][nt], 0, 0, 0);
-                if (mt + PF < MT) readA(mt + PF);
-                __builtin_amdgcn_sched_barrier(0);
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, W[pa[s]]),
+                                                                              __builtin_bit_cast(bf16x8, C[nt].p[pbx[s]]), acc[mt][nt], 0, 0, 0);
             } else if constexpr (DT == DT_BF16) {
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[mt][0]),
-                                                                          __builtin_bit_cast(bf16x8, Bl[nt]), acc[mt][nt], 0, 0, 0);
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, W[0]),
+                                                                          __builtin_bit_cast(bf16x8, C[nt].p[0]), acc[mt][nt], 0, 0, 0);
             } else {
                 auto cat = [](const u32x4& lo, const u32x4& hi) {
                     return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
@@ -262,28 +299,51 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
                     acc[mt][nt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                        cat(A[mt][0], A[mt][1]), cat(Bl[nt], Bh[nt]), acc[mt][nt], 0, 0, 0, kE8M0One, 0, kE8M0One);
+                        cat(W[0], W[SUB - 1]), cat(C[nt].p[0], C[nt].p[1]), acc[mt][nt], 0, 0, 0, kE8M0One, 0, kE8M0One);
             }
+            // the fragments of the rows to come; before the last PF rows, the next chunk's
+            if (mt + PF == MT) {
+                if (++ra_st == ST) ra_st = 0;
+            }
+            if (mt + PF < MT || AAHEAD) readA((mt + PF) % MT);
+            if (BAHEAD && mt + PF == MT - 1) readB();
+            if (BAHEAD && mt + NT >= MT) N[mt + NT - MT] = prepare(mt + NT - MT);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    // chunks 0 .. ST - 2 in flight; step k waits for chunk k, lets every
-    // wave finish chunk k - 1 (whose stage chunk k + ST - 1 then takes)
+    // Step k issues weights k + ST - 1 and pixels k + PS - 1 into the stages of
+    // chunk k - 1; it needs chunk k, or k + 1 of what is read ahead, and waits
+    // with the loads behind those in flight.
+    constexpr int LATER = ST == PS ? (AAHEAD ? ST - 3 : ST - 2) * (AW + NB) : 0;
+    static_assert(ST == PS || (ST == 2 && PS == 3), "the last step's loads are needed");
 #pragma unroll
-    for (int j = 0; j < ST - 1; ++j)
-        if (j < nk) issue();
-    int c_st = 0, k = 0;
-    for (; k + ST - 1 < nk; ++k) {
-        wait_vm<(ST - 2) * L>();
+    for (int j = 0; j < PS - 1; ++j) {
+        if (j < ST - 1 && j < nk) issue_w();
+        if (j < nk) issue_p();
+    }
+    wait_vm<0>();                                       // (the compiler then adds no waits of its own to the loop)
+    lds_barrier();
+    if constexpr (BAHEAD) {
+        readB();
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) N[nt] = prepare(nt);
+    }
+    if constexpr (AAHEAD) {
+#pragma unroll
+        for (int mt = 0; mt < PF; ++mt) readA(mt);
+    }
+    int k = 0;
+    for (; k + PS - 1 < nk; ++k) {
+        wait_vm<LATER>();
         lds_barrier();
-        step(smem + c_st * STW, std::true_type{});
-        if (++c_st == ST) c_st = 0;
+        step(std::true_type{});
     }
     for (; k < nk; ++k) {
         wait_vm<0>();
         lds_barrier();
-        step(smem + c_st * STW, std::false_type{});
-        if (++c_st == ST) c_st = 0;
+        if (ST < PS && k + ST - 1 < nk) issue_w();
+        step(std::false_type{});
     }
     lds_barrier();                                      // every stage is free
 
