@@ -25,7 +25,8 @@
 // 95 -> 87).
 //
 // The products, their order and the order of the channels and taps are those
-// of conv_igemm, so the results are the same bits.
+// of conv_igemm, so the results are the same bits; with KS = 4 those of the
+// split-K kernels, whose four sums a wave then keeps in its own registers.
 //
 // Measured against the direct form (kernel time, us): 720p split-FP32 GA1
 // 289 -> 252, GS2 382 -> 333; bf16 GA1 89 -> 68, GS2 129 -> 104; e4m3 GA1 50 ->
@@ -46,7 +47,7 @@ namespace lic {
 
 // WAVES: 4 with two blocks per CU, or 8 with one where two blocks' stages do
 // not fit its 160 KB of LDS (either way two waves per SIMD, 256 registers).
-template <int TAG, int CIN, int MT, int NT, int WAVES, int ST, int LD, int EP, int DT>
+template <int TAG, int CIN, int MT, int NT, int WAVES, int ST, int KS, int LD, int EP, int DT>
 __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(ConvArgs a)
 {
     using Elem = typename std::conditional<LD == LD_I8, int8_t, typename Prec<DT>::Elem>::type;
@@ -176,14 +177,18 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
         }
     }
 
-    f4 acc[MT][NT];
+    // KS sums per output, chunk k to sum k % KS (the K slots of a split layer)
+    f4 part[KS][MT][NT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        f4 b = {0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (DT != DT_FP8) b = *reinterpret_cast<const f4*>(a.bias + mt * 16 + kg * 4);
+    for (int s = 0; s < KS; ++s)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = b;
-    }
+        for (int mt = 0; mt < MT; ++mt) {
+            f4 b = {0.0f, 0.0f, 0.0f, 0.0f};
+            if constexpr (DT != DT_FP8)
+                if (s == 0) b = *reinterpret_cast<const f4*>(a.bias + mt * 16 + kg * 4);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) part[s][mt][nt] = b;
+        }
 
     // With a third stage the next chunk's fragments are read (and the pixels'
     // split or converted) in the shadow of this one's products, before its
@@ -261,14 +266,14 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
         }
         return r;
     };
-    auto step = [&](auto more) __attribute__((always_inline)) {
+    auto step = [&](f4 (&acc)[MT][NT], auto more) __attribute__((always_inline)) {
         if constexpr (!BAHEAD) readB();
         if constexpr (!AAHEAD) {
 #pragma unroll
             for (int mt = 0; mt < PF; ++mt) readA(mt);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (decltype(more)::value) {
+        if (more) {
             issue_w();
             issue_p();
         }
@@ -333,18 +338,46 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) gdn_staged(Con
 #pragma unroll
         for (int mt = 0; mt < PF; ++mt) readA(mt);
     }
-    int k = 0;
-    for (; k + PS - 1 < nk; ++k) {
-        wait_vm<LATER>();
-        lds_barrier();
-        step(std::true_type{});
+    if constexpr (KS == 1) {
+        int k = 0;
+        for (; k + PS - 1 < nk; ++k) {
+            wait_vm<LATER>();
+            lds_barrier();
+            step(part[0], std::true_type{});
+        }
+        for (; k < nk; ++k) {
+            wait_vm<0>();
+            lds_barrier();
+            if (ST < PS && k + ST - 1 < nk) issue_w();
+            step(part[0], std::false_type{});
+        }
+    } else {
+        static_assert(ST == PS, "one condition for both rings");
+#pragma unroll 1
+        for (int k = 0; k < nk; k += KS)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                if (k + s >= nk) break;
+                if (k + s + ST - 2 < nk) wait_vm<LATER>();
+                else wait_vm<0>();
+                lds_barrier();
+                step(part[s], k + s + ST - 1 < nk);
+                // (else the compiler moves the products behind the loop's exits)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(part[s][mt][nt]));
+            }
     }
-    for (; k < nk; ++k) {
-        wait_vm<0>();
-        lds_barrier();
-        if (ST < PS && k + ST - 1 < nk) issue_w();
-        step(std::false_type{});
-    }
+    f4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            acc[mt][nt] = part[0][mt][nt];
+#pragma unroll
+            for (int s = 1; s < KS; ++s) acc[mt][nt] += part[s][mt][nt];
+        }
     lds_barrier();                                      // every stage is free
 
     const long oc = a.co_ld ? a.co_ld : a.Co;
@@ -364,7 +397,12 @@ struct GdnEntry {
 };
 
 #define LIC_G(TAG, CIN, MT, NT, WV, ST, LD, EP, DT) \
-    {{TAG, CIN, MT, NT, WV, 1, LD, EP, DT}, gdn_staged<TAG, CIN, MT, NT, WV, ST, LD, EP, DT>}
+    {{TAG, CIN, MT, NT, WV, 1, LD, EP, DT}, gdn_staged<TAG, CIN, MT, NT, WV, ST, 1, LD, EP, DT>}
+// four K slots (layers whose grid of one image would leave SIMDs idle)
+#define LIC_G4(TAG, CIN, MT, ST, LD, EP, DT) {{TAG, CIN, MT, 1, 4, 4, LD, EP, DT}, gdn_staged<TAG, CIN, MT, 1, 4, ST, 4, LD, EP, DT>}
+#define LIC_GK(TAG, EP)                                                                                        \
+    LIC_G4(TAG, 128, 8, 4, LD_F32, EP, DT_BF16), LIC_G4(TAG, 192, 12, 4, LD_F32, EP, DT_BF16),                 \
+        LIC_G4(TAG, 128, 8, 3, LD_F32, EP, DT_FP8), LIC_G4(TAG, 192, 12, 2, LD_F32, EP, DT_FP8)
 // one layer at 128 and 192 channels; NT = 1 for grids that would leave SIMDs
 // idle with two 16-pixel tiles per wave (its stages are smaller: more of them)
 #define LIC_GX(TAG, EP)                                                                                        \
@@ -381,6 +419,9 @@ static const GdnEntry kGdn[] = {
     LIC_GX(LIC_GA1, EP_GDN), LIC_GX(LIC_GA2, EP_GDN), LIC_GX(LIC_GS1, EP_IGDN), LIC_GX(LIC_GS2, EP_IGDN),
     LIC_GB(LIC_GA1, EP_GDN), LIC_GB(LIC_GA2, EP_GDN), LIC_GB(LIC_GS1, EP_IGDN), LIC_GB(LIC_GS2, EP_IGDN),
     LIC_GF(LIC_GA1, EP_GDN), LIC_GF(LIC_GA2, EP_GDN), LIC_GF(LIC_GS1, EP_IGDN), LIC_GF(LIC_GS2, EP_IGDN),
+    LIC_GK(LIC_GA1, EP_GDN), LIC_GK(LIC_GA2, EP_GDN), LIC_GK(LIC_GS1, EP_IGDN), LIC_GK(LIC_GS2, EP_IGDN),
+    LIC_G4(LIC_GS0, 192, 8, 4, LD_I8, EP_IGDN, DT_BF16), LIC_G4(LIC_GS0, 192, 8, 4, LD_F32, EP_IGDN, DT_BF16),
+    LIC_G4(LIC_GS0, 320, 12, 4, LD_I8, EP_IGDN, DT_BF16),
     // g_s from symbols, and from y_hat (context model)
     LIC_G(LIC_GS0, 192, 8, 2, 4, 2, LD_I8, EP_IGDN, DT_F32X), LIC_G(LIC_GS0, 192, 8, 1, 4, 2, LD_I8, EP_IGDN, DT_F32X),
     LIC_G(LIC_GS0, 192, 8, 2, 4, 4, LD_I8, EP_IGDN, DT_BF16), LIC_G(LIC_GS0, 192, 8, 1, 4, 4, LD_I8, EP_IGDN, DT_BF16),

@@ -885,9 +885,25 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
     // 470 x 834 36 [168], 35 [336], 31 [672]; h_a's second 31 [60], 19 [120], 14
     // [240], 16 x 16 15 [480]; its third 31, 18, 12 [60], 10 [120]; bf16 g_a's
     // last 18 [360], 21 [720].
+    // Reduced-precision GDN layers that the rule above gives four K slots, on grids
+    // (of the whole batch) of enough blocks for the staged kernel: its waves keep the four
+    // sums side by side, so a block's weights serve 64 pixels instead of 16 or 32.
+    // Measured (layer call, us; blocks in brackets): e4m3 GA1 28 -> 34 [64], 37 -> 35 [96],
+    // 45 -> 35 [160], 54 -> 36 [240], GS1 43 -> 32 [384]; bf16 GA1 33 -> 49 [64], 41 -> 49
+    // [96], 45 -> 45 [160], GA2 54 -> 51 [192]; 192 channels e4m3 GA2 80 -> 50 [240], bf16
+    // GA1 66 -> 70 [96], 93 -> 73 [160], GA2 122 -> 75 [240].
+    if (key.ksplit == 4 && (L.ep == EP_GDN || L.ep == EP_IGDN) && a.wt) {
+        KernelKey k4 = key;
+        k4.nt = 1;
+        k4.waves = 4;
+        if (gdn_available(k4) && (pixels + 63) / 64 * L.nphase >= (L.dt == DT_FP8 ? 96 : 160)) {
+            key = k4;
+            staged = true;
+        }
+    }
     SplitKey sk{};
     bool two_pass = false;
-    if (key.ksplit > 1 && a.ws) {
+    if (key.ksplit > 1 && a.ws && !staged) {
         const bool gdn = L.ep == EP_GDN || L.ep == EP_IGDN;
         sk = SplitKey{4, 1, gdn ? key.mt / 4 : 1, key.ksplit, L.ld, L.ep, L.dt};
         auto blocks = [&](int mt, int nt) { return (pixels + 16 * nt - 1) / (16 * nt) * L.nphase * (gdn ? 1 : L.cop / (16 * mt)); };
@@ -919,7 +935,7 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
         if (split_available(sk)) a.ncog = gdn && !two_pass ? 1 : L.cop / (16 * sk.mt);
         else sk = SplitKey{};
     }
-    const long per_block = (long)(key.waves / key.ksplit) * key.nt * 16;
+    const long per_block = (long)(staged ? key.waves : key.waves / key.ksplit) * key.nt * 16;
     // halo tiles: one block per key.waves grid rows x 16 key.nt pixels
     const long tiles = sk.mt ? (pixels + 16 * sk.nt - 1) / (16 * sk.nt)
                        : key.ld == LD_TILE

@@ -130,8 +130,17 @@ TWO_PASS = [("GA1", 128, 192, 9, 64, 64, 0), ("GA2", 128, 192, 33, 64, 64, 1), (
             ("GS0", 192, 320, 11, 64, 192, 1), ("GS1", 192, 320, 2, 192, 192, 0)]
 
 
-@pytest.mark.parametrize("layer,N,M,n,H,W,norm", TWO_PASS)
-def test_two_pass_gdn_same_bits(layer, N, M, n, H, W, norm):
+# reduced forms, the same layout: alone on the split-K kernels, the batch on the staged
+# ones with four K slots; grids whose last block is not full
+FOUR_SUMS = [(BF16, "GA1", 128, 192, 41, 64, 64, 0), (BF16, "GA2", 128, 192, 54, 64, 192, 1), (BF16, "GS0", 128, 192, 161, 64, 64, 0),
+             (BF16, "GS1", 128, 192, 41, 64, 64, 0), (BF16, "GS2", 128, 192, 3, 128, 192, 0), (BF16, "GA1", 192, 320, 14, 128, 192, 0),
+             (BF16, "GS0", 192, 320, 27, 64, 384, 1), (BF16, "GS2", 192, 320, 11, 64, 64, 0), (FP8, "GA1", 128, 192, 25, 64, 64, 1),
+             (FP8, "GA2", 128, 192, 33, 64, 192, 0), (FP8, "GS1", 128, 192, 25, 64, 64, 0), (FP8, "GS2", 128, 192, 3, 128, 192, 1),
+             (FP8, "GA2", 192, 320, 33, 64, 192, 0), (FP8, "GS1", 192, 320, 9, 128, 192, 0)]
+
+
+@pytest.mark.parametrize("prec,layer,N,M,n,H,W,norm", [(FP32,) + c for c in TWO_PASS] + FOUR_SUMS)
+def test_batch_route_same_bits(prec, layer, N, M, n, H, W, norm):
     import torch
 
     from paper_2208_01641_amd import Codec
@@ -144,12 +153,15 @@ def test_two_pass_gdn_same_bits(layer, N, M, n, H, W, norm):
     x = torch.randn((n, d["Hp"] // di, d["Wp"] // di, ci), device="cuda", generator=g)
     if layer == "GS0":
         x = (3 * x).round().clamp(-64, 64).to(torch.int8)
-    out = torch.empty((n, d["Hp"] // do, d["Wp"] // do, N), device="cuda")
-    one = torch.empty((1,) + out.shape[1:], device="cuda")
-    c = Codec(synth.weight_blob(P, 1, N, M), kind=1, N=N, M=M, max_h=64, max_w=64, max_in_flight=1, norm=norm)
+    elif prec != FP32:
+        x = x.to(torch.bfloat16) if prec == BF16 else (ACT_Q * x).to(torch.float8_e4m3fn)
+    out_dt = torch.float32 if prec == FP32 else torch.bfloat16 if prec == BF16 or layer == "GS2" else torch.float8_e4m3fn
+    out = torch.empty((n, d["Hp"] // do, d["Wp"] // do, N), dtype=out_dt, device="cuda")
+    one = torch.empty((1,) + out.shape[1:], dtype=out_dt, device="cuda")
+    c = Codec(synth.weight_blob(P, 1, N, M), kind=1, N=N, M=M, precision=prec, max_h=64, max_w=64, max_in_flight=1, norm=norm)
     c.run_layer(layer, n, H, W, x, out)
-    assert bool(out.isfinite().all())
+    assert bool(out.float().isfinite().all())
     for i in range(n):
         c.run_layer(layer, 1, H, W, x[i:i + 1].contiguous(), one)
-        assert torch.equal(out[i], one[0]), f"image {i} of {n} differs"
+        assert torch.equal(out[i].view(torch.uint8), one[0].view(torch.uint8)), f"image {i} of {n} differs"
     c.close()
