@@ -37,7 +37,7 @@ PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "fp8": 5000.0, "f32x": 2500.0 / 6}
 PEAK_BASIS = {"f32": "FP32 matrix cores", "bf16": "bf16 matrix cores", "fp8": "fp8 matrix cores",
               "f32x": "bf16 matrix cores / 6 (six bf16 products per FP32 product)"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
-KERNEL_SRC = os.path.join(ROOT, "paper_2208_01641_amd", "csrc", "conv_kernels.hip")
+KERNEL_DIR = os.path.join(ROOT, "paper_2208_01641_amd", "csrc")
 LAYERS = ("GA0", "GA1", "GA2", "GA3", "HA0", "HA1", "HA2", "HS0", "HS1", "HS2", "GS0", "GS1", "GS2", "GS3")
 # the context model's layers beyond those (context convolution, entropy
 # parameters of the anchor pass and of the second pass)
@@ -76,8 +76,13 @@ def layer_flops(layer, H, W, N, M, kind=1):
 
 
 def kernel_src_hash():
-    with open(KERNEL_SRC, "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()[:16]
+    """Over every kernel source and the headers they share."""
+    h = hashlib.sha256()
+    for f in sorted(os.listdir(KERNEL_DIR)):
+        if f.endswith(".hip") or f in ("conv_args.h", "gdn_finish.h", "lds_stage.h", "mfma_common.h"):
+            with open(os.path.join(KERNEL_DIR, f), "rb") as fh:
+                h.update(fh.read())
+    return h.hexdigest()[:16]
 
 
 def traffic_for(layer, precision):
