@@ -908,8 +908,8 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
         sk = SplitKey{4, 1, gdn ? key.mt / 4 : 1, key.ksplit, L.ld, L.ep, L.dt};
         auto blocks = [&](int mt, int nt) { return (pixels + 16 * nt - 1) / (16 * nt) * L.nphase * (gdn ? 1 : L.cop / (16 * mt)); };
         if (gdn) {
-            // (e4m3, g_s's second layer at 512 x 768: 35 us with 16-pixel
-            // tiles, 26 with 32-pixel tiles)
+            // (FP32; layer call, us, 16- and 32-pixel tiles: GA1 at 256 x 256, four
+            // images, 147 and 143 [512], GS2 at 128 x 128 68 and 68 [512], 115 and 117 [1024])
             if (blocks(4, 2) >= 512) sk.nt = 2;
             if (!split_available(sk)) sk.nt = 1;
         } else if (L.cop % 64 == 0 && blocks(4, 2) >= (L.dt == DT_F32 ? 1024 : 320)) {

@@ -640,12 +640,13 @@ struct SplitEntry {
     LIC_S(4, 2, 1, 8, 2, 2, LD, EP, DT), LIC_S(4, 1, 1, 8, 2, 2, LD, EP, DT), LIC_S(2, 1, 1, 8, 2, 2, LD, EP, DT), \
         LIC_S(1, 1, 1, 8, 4, 4, LD, EP, DT), LIC_S(4, 2, 1, 4, 2, 2, LD, EP, DT), LIC_S(4, 1, 1, 4, 2, 2, LD, EP, DT), \
         LIC_S(2, 1, 1, 4, 2, 2, LD, EP, DT)
-// GDN layers: 128 and 192 rows
-#define LIC_SG(LD, EP, DT)                                                                                    \
-    LIC_S(4, 1, 2, 4, 4, 4, LD, EP, DT), LIC_S(4, 2, 2, 4, 4, 2, LD, EP, DT), LIC_S(4, 1, 3, 4, 4, 3, LD, EP, DT), \
-        LIC_S(4, 2, 3, 4, 2, 3, LD, EP, DT)
-#define LIC_SGF(LD, EP, DT)                                                                                   \
-    LIC_S(4, 1, 2, 4, 2, 2, LD, EP, DT), LIC_S(4, 2, 2, 4, 2, 2, LD, EP, DT), LIC_S(4, 1, 3, 4, 2, 3, LD, EP, DT)
+// GDN layers: 128 and 192 rows; 32-pixel tiles in FP32 only (the reduced forms
+// leave for the staged kernel before)
+#define LIC_SG(LD, EP)                                                                                        \
+    LIC_S(4, 1, 2, 4, 4, 4, LD, EP, DT_F32), LIC_S(4, 2, 2, 4, 4, 2, LD, EP, DT_F32),                          \
+        LIC_S(4, 1, 3, 4, 4, 3, LD, EP, DT_F32), LIC_S(4, 2, 3, 4, 2, 3, LD, EP, DT_F32)
+#define LIC_SGB(LD, EP) LIC_S(4, 1, 2, 4, 4, 4, LD, EP, DT_BF16), LIC_S(4, 1, 3, 4, 4, 3, LD, EP, DT_BF16)
+#define LIC_SGF(LD, EP) LIC_S(4, 1, 2, 4, 2, 2, LD, EP, DT_FP8), LIC_S(4, 1, 3, 4, 2, 3, LD, EP, DT_FP8)
 
 // the sums of the smallest GDN layers (a second pass normalises)
 #define LIC_SS(LD) LIC_S(1, 1, 1, 4, 8, 4, LD, EP_NONE, DT_F32)
@@ -655,9 +656,9 @@ static const SplitEntry kSplit[] = {
     LIC_SE(LD_F32, EP_RELU, DT_F32),  LIC_SE(LD_F32_ABS, EP_RELU, DT_F32), LIC_SE(LD_I8, EP_RELU, DT_F32),
     LIC_SE(LD_F32, EP_QUANT, DT_F32), LIC_SE(LD_F32, EP_QUANT, DT_BF16),   LIC_SEF(LD_F32, EP_QUANT, DT_FP8),
     LIC_SE(LD_F32, EP_INDEX, DT_F32), LIC_SE(LD_F32, EP_NONE, DT_F32),     LIC_SE(LD_F32, EP_MSCALE, DT_F32),
-    LIC_SG(LD_F32, EP_GDN, DT_F32),   LIC_SG(LD_F32, EP_IGDN, DT_F32),     LIC_SG(LD_I8, EP_IGDN, DT_F32),
-    LIC_SG(LD_F32, EP_GDN, DT_BF16),  LIC_SG(LD_F32, EP_IGDN, DT_BF16),    LIC_SG(LD_I8, EP_IGDN, DT_BF16),
-    LIC_SGF(LD_F32, EP_GDN, DT_FP8),  LIC_SGF(LD_F32, EP_IGDN, DT_FP8),
+    LIC_SG(LD_F32, EP_GDN),  LIC_SG(LD_F32, EP_IGDN),  LIC_SG(LD_I8, EP_IGDN),
+    LIC_SGB(LD_F32, EP_GDN), LIC_SGB(LD_F32, EP_IGDN), LIC_SGB(LD_I8, EP_IGDN),
+    LIC_SGF(LD_F32, EP_GDN), LIC_SGF(LD_F32, EP_IGDN),
 };
 
 bool split_available(const SplitKey& k)
