@@ -534,9 +534,11 @@ int Codec::build_layers(const ParamMap& P)
                         rem -= hv;
                     }
                 }
-                if (gdn) L.d_wx = (uint16_t*)dev_alloc(hx.size() * sizeof(uint16_t));
-                if (gdn && !L.d_wx) { err = "device allocation failed"; return LIC_E_NOMEM; }
-                if (gdn) HIP_TRY(hipMemcpy(L.d_wx, hx.data(), hx.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+                if (sp.ld == LD_RGB) {                  // (the others have them in fragment order only)
+                    L.d_wx = (uint16_t*)dev_alloc(hx.size() * sizeof(uint16_t));
+                    if (!L.d_wx) { err = "device allocation failed"; return LIC_E_NOMEM; }
+                    HIP_TRY(hipMemcpy(L.d_wx, hx.data(), hx.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+                }
             }
         }
         for (size_t i = 0; i < ph.size(); ++i) ph[i].woff = (int64_t)pm.off[i];
