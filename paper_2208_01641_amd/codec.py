@@ -236,8 +236,7 @@ class Codec:
 
     def layer_kernel(self, layer, H, W):
         """(operand form name, K-split waves) of the kernel a layer launches
-        for one H x W frame.  (g_s's output layer counts as "f32": its kernel
-        splits the FP32 operands itself.)"""
+        for one H x W frame."""
         lid = _lib.LAYER_ID[layer] if isinstance(layer, str) else int(layer)
         form, ks = ctypes.c_int(), ctypes.c_int()
         self._check(lib.codec_layer_kernel(self._h, lid, H, W, ctypes.byref(form), ctypes.byref(ks)))

@@ -516,8 +516,7 @@ int Codec::build_layers(const ParamMap& P)
             HIP_TRY(hipMemcpy(L.d_w, h8.data(), total, hipMemcpyHostToDevice));
         } else {
             HIP_TRY(hipMemcpy(L.d_w, wp.data(), total * esz, hipMemcpyHostToDevice));
-            const bool gdn = sp.ep == EP_GDN || sp.ep == EP_IGDN;
-            if (gdn || (sp.ep == EP_RGB && rgb_available(L.cin, DT_F32))) {
+            if (sp.ep == EP_GDN || sp.ep == EP_IGDN) {
                 // split-FP32 operands of the whole-frame kernels: each group of
                 // 8 packed values as [part 0 x8][part 1 x8][part 2 x8], the
                 // parts rounded to nearest from what the previous ones leave
@@ -545,7 +544,7 @@ int Codec::build_layers(const ParamMap& P)
         // the same operands in fragment order: of the staged kernels (GDN layers;
         // FP32 as bf16 parts) and of the split-K kernels
         auto fragments = [&](int form, uint8_t** dst) -> int {
-            const TileOrder to = tile_order(pm, form, sp.ep == EP_RGB && form == DT_F32X);
+            const TileOrder to = tile_order(pm, form);
             const size_t es = form == DT_F32 ? 4 : form == DT_FP8 ? 1 : 2, sub = form == DT_F32X ? 3 : 1;
             std::vector<uint8_t> wt(to.idx.size() * es);
             for (size_t j = 0; j < to.idx.size(); ++j) {
@@ -573,7 +572,7 @@ int Codec::build_layers(const ParamMap& P)
             int rc = LIC_OK;
             if (gdn) rc = fragments(L.dt == DT_F32 ? DT_F32X : L.dt, &L.d_wt);
             if (rc == LIC_OK && gdn && L.dt != DT_F32) L.d_ws = L.d_wt;
-            else if (rc == LIC_OK) rc = fragments(sp.ep == EP_RGB && !hx.empty() ? DT_F32X : L.dt, &L.d_ws);
+            else if (rc == LIC_OK) rc = fragments(L.dt, &L.d_ws);
             if (rc != LIC_OK) return rc;
         }
         HIP_TRY(hipMemcpy(L.d_ph, ph.data(), ph.size() * sizeof(PhaseDesc), hipMemcpyHostToDevice));

@@ -165,7 +165,7 @@ PackMap pack_map_checkerboard(int ci, int co, int k, int part, bool pair_rows)
     return m;
 }
 
-TileOrder tile_order(const PackMap& m, int dt, bool quads)
+TileOrder tile_order(const PackMap& m, int dt)
 {
     TileOrder o;
     const int kch = dt == DT_F32 ? 16 : dt == DT_FP8 ? 128 : 32;
@@ -183,10 +183,10 @@ TileOrder tile_order(const PackMap& m, int dt, bool quads)
                         // the first of the lane's elements (16 e4m3 elements are of one tap)
                         const int x = k * kch + (l / 16) * 32 + s * 16;
                         const int t = dt == DT_FP8 ? x / m.cin : k % ntaps;
-                        const int c = dt == DT_FP8 ? x % m.cin : (k / ntaps) * kch + (l / 16) * (quads ? 4 : ke);
+                        const int c = dt == DT_FP8 ? x % m.cin : (k / ntaps) * kch + (l / 16) * ke;
                         const size_t j = m.off[f] + ((size_t)t * m.cop + mt * 16 + l % 16) * m.cin + c;
                         for (int e = 0; e < ke; ++e)
-                            o.idx.push_back(t < ntaps ? (int32_t)(j + (quads ? (e / 4) * 16 + e % 4 : e)) : -1);
+                            o.idx.push_back(t < ntaps ? (int32_t)(j + e) : -1);
                     }
     }
     return o;

@@ -57,13 +57,11 @@ PackMap pack_map_checkerboard(int ci, int co, int k, int part, bool pair_rows);
 // the elements of lane group l / 16.  sub: the three bf16 parts of split-FP32,
 // the two 16-byte halves of e4m3, else one.  Returns for every element its
 // index in the packed array (e4m3 past the end: -1; split-FP32: the FP32
-// element, once per part) and the element offset of each phase.  quads: lane
-// group g holds channels 4 g .. 4 g + 3 of both 16-channel halves of a
-// 32-channel chunk instead of 8 in a row.
+// element, once per part) and the element offset of each phase.
 struct TileOrder {
     std::vector<int32_t> idx;
     std::vector<size_t> off;
 };
-TileOrder tile_order(const PackMap& m, int dt, bool quads = false);
+TileOrder tile_order(const PackMap& m, int dt);
 
 }  // namespace lic
