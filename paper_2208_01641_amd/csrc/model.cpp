@@ -208,6 +208,62 @@ bool build_tables(const ParamMap& P, int kind, int N, int M, std::vector<float>*
     return true;
 }
 
+namespace {
+
+// Every layer takes what the layer before it gives, the ends of the chains are
+// the image, y (M channels), z (N) and, in the context model, psi and the
+// context (2M each), and no hidden layer is wider than N, for which the pools
+// are sized.  (Layers that are missing are reported where they are packed.)
+bool check_widths(const ParamMap& P, int kind, int N, int M, std::string* err)
+{
+    struct Link {
+        const char* name;
+        bool deconv;
+        int from;          // input width; 0: the output of the layer before
+        int to;            // output width; 0: a hidden layer
+        bool pooled;       // a hidden layer's output goes to a buffer of width N
+    };
+    std::vector<Link> links = {
+        {"ga0", false, 3, 0, true}, {"ga1", false, 0, 0, true}, {"ga2", false, 0, 0, true}, {"ga3", false, 0, M, true},
+        {"gs0", true, M, 0, true},  {"gs1", true, 0, 0, true},  {"gs2", true, 0, 0, true},  {"gs3", true, 0, 3, true},
+    };
+    if (kind >= 1) {
+        const std::vector<Link> hyper = {
+            {"ha0", false, M, 0, true}, {"ha1", false, 0, 0, true}, {"ha2", false, 0, N, true},
+            {"hs0", true, N, 0, true},  {"hs1", true, 0, 0, true},  {"hs2", false, 0, kind == 2 ? 2 * M : M, true},
+        };
+        links.insert(links.end(), hyper.begin(), hyper.end());
+    }
+    if (kind == 2) {
+        const std::vector<Link> ctx = {
+            {"cx", false, M, 2 * M, false}, {"ep0", false, 4 * M, 0, false}, {"ep1", false, 0, 0, false},
+            {"ep2", false, 0, 2 * M, false},
+        };
+        links.insert(links.end(), ctx.begin(), ctx.end());
+    }
+    int last = 0;
+    for (const Link& k : links) {
+        auto it = P.find(std::string(k.name) + ".w");
+        if (it == P.end() || it->second.first.size() != 4) return true;
+        const std::vector<int>& dims = it->second.first;
+        const int ci = dims[k.deconv ? 0 : 1], co = dims[k.deconv ? 1 : 0];
+        const int want = k.from ? k.from : last;
+        if (ci != want) {
+            *err = std::string("weight blob: ") + k.name + " takes " + std::to_string(ci) + " channels, not " + std::to_string(want);
+            return false;
+        }
+        if (k.to ? co != k.to : co < 1 || (k.pooled && co > N)) {
+            *err = std::string("weight blob: ") + k.name + " gives " + std::to_string(co) + " channels, not " +
+                   (k.to ? std::to_string(k.to) : "1 to " + std::to_string(N));
+            return false;
+        }
+        last = co;
+    }
+    return true;
+}
+
+}  // namespace
+
 int Codec::load(const void* blob, size_t len)
 {
     ParamMap P;
@@ -220,6 +276,7 @@ int Codec::load(const void* blob, size_t len)
     kind = cfg.kind;
     N = cfg.N;
     M = cfg.M;
+    if (!check_widths(P, kind, N, M, &err)) return LIC_E_MODEL;
     hs_exp = cfg.hs_out == LIC_HS_EXP ? 1 : 0;
     norm = cfg.norm;
     lanes = cfg.rans_lanes;
@@ -774,6 +831,27 @@ int Codec::launch_layer(int id, int n, const FrameDims& d, const void* in, void*
     return launch_conv_policy(shape, a, (long)g.Hg * g.Wg, s, errp, chosen);
 }
 
+// The widths that the codec's kernels are written for.  Some of them take any
+// number of input channels at run time (conv_split), and would read and write
+// past their tiles at others.
+static bool codec_widths(const ConvShape& L)
+{
+    const int ci = L.cin, co = L.cop;
+    switch (L.tag) {
+    case LIC_GA0: return ci == 96 && (co == 128 || co == 192);
+    case LIC_GA1: case LIC_GA2: case LIC_GS1: case LIC_GS2: return ci == co && (co == 128 || co == 192);
+    case LIC_GS0: return (ci == 192 && co == 128) || (ci == 320 && co == 192 && L.ld == LD_I8);
+    case LIC_GA3: case LIC_HA1: case LIC_HA2: case LIC_HS0: case LIC_HS1: case LIC_GS3: return ci == 128 || ci == 192;
+    case LIC_HA0: return ci == 192 || (ci == 320 && L.ld == LD_F32_ABS);
+    case LIC_HS2: return ci == 128 || (ci == 192 && L.ep == EP_INDEX);
+    case LIC_CX: return ci == 192;
+    case LIC_EP0A: case LIC_EP0N: return ci == 768;
+    case LIC_EP1A: case LIC_EP1N: return ci == 640;
+    case LIC_EP2A: case LIC_EP2N: return ci == 512;
+    }
+    return true;                                        // the distilled network: by its kernels' keys
+}
+
 int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipStream_t s, std::string* errp,
                        KernelKey* chosen)
 {
@@ -945,7 +1023,7 @@ int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipS
     const long nblocks = tiles * L.nphase * a.ncog;
     if (nblocks <= 0 && !chosen) return LIC_OK;
     if (nblocks > (1L << 30)) { *errp = "launch too large"; return LIC_E_BUDGET; }
-    if (!staged && !rgb && !image && !sk.mt && !kernel_available(key)) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
+    if (!codec_widths(L) || (!staged && !rgb && !image && !sk.mt && !kernel_available(key))) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
     if (chosen) {
         *chosen = key;
         return LIC_OK;
