@@ -276,6 +276,9 @@ int codec_calibrate(codec_t* c, const float* x, int n, int H, int W, int is_devi
  * stores have clamped to +-448 since create.  Returns LIC_NUM_LAYERS. */
 int codec_fp8_scales(const codec_t* c, float* q, int max, unsigned long long* saturated);
 
+/* Runs one layer and waits for it.  Buffers may start at any element; an
+ * input at an address that is no multiple of 16 (the image: of 4), or a GDN
+ * layer's output at one, goes through an aligned copy on the device. */
 int codec_run_layer(codec_t* c, int layer, int n, int H, int W,
                     const void* in, void* out, void* aux);
 /* The same with the second input and output of LIC_EP2A / LIC_EP2N (see the

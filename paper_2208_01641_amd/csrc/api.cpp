@@ -29,6 +29,25 @@ bool supported_shape(int kind, int N, int M)
     return kind == LIC_KIND_HYPERPRIOR ? hyper_ok : (kind == LIC_KIND_FACTORIZED && hyper_ok);
 }
 
+// A caller's device buffer as the kernels can take it: the buffer itself, or
+// where its address is no multiple of align a new one of the same size.
+struct AlignedCopy {
+    void* ptr;
+    bool copied = false;
+    AlignedCopy(const void* p, size_t bytes, size_t align) : ptr(const_cast<void*>(p))
+    {
+        if (!p || reinterpret_cast<uintptr_t>(p) % align == 0) return;
+        copied = hipMalloc(&ptr, bytes) == hipSuccess;
+        if (!copied) ptr = nullptr;
+    }
+    ~AlignedCopy()
+    {
+        if (copied) (void)hipFree(ptr);
+    }
+    AlignedCopy(const AlignedCopy&) = delete;
+    AlignedCopy& operator=(const AlignedCopy&) = delete;
+};
+
 bool check_frame(Codec* c, int n, int H, int W, int* rc)
 {
     if (n < 0 || H < 1 || W < 1) { *rc = fail(c, LIC_E_ARG, "bad frame count or size"); return false; }
@@ -352,10 +371,26 @@ int codec_run_layer_ex(codec_t* c, int layer, int n, int H, int W, const void* i
         return fail(c, LIC_E_ARG, "the last entropy-parameter layer needs out2 (y_hat or the means)");
     lic::FrameDims d(H, W);
     if (hipSetDevice(c->cfg.hip_device) != hipSuccess) return fail(c, LIC_E_HIP, "hipSetDevice");
+    // The kernels load pixels straight into LDS and the GDN layers store them in
+    // 16-byte pieces, which takes aligned addresses (the image: whole floats);
+    // the pools' are.  A caller's others go through an aligned copy.
+    const hipStream_t s = c->layer_stream;
+    const int ep = c->layers[layer].ep;
+    size_t bi, bo, ba;
+    c->layer_bytes(layer, n, d, &bi, &bo, &ba);
+    AlignedCopy ci(in, bi, layer == LIC_GA0 ? 4 : 16);
+    AlignedCopy co(out, bo, ep == lic::EP_GDN || ep == lic::EP_IGDN ? 16 : 1);
+    if (!ci.ptr || (out && !co.ptr)) return fail(c, LIC_E_NOMEM, "aligned copy of a layer's buffers");
+    hipError_t he = ci.copied ? hipMemcpyAsync(ci.ptr, in, bi, hipMemcpyDeviceToDevice, s) : hipSuccess;
+    if (he != hipSuccess) return fail(c, LIC_E_HIP, hipGetErrorString(he));
     std::string e;
-    int rc = c->launch_layer(layer, n, d, in, out, aux, c->layer_stream, &e, nullptr, in2, out2);
+    int rc = c->launch_layer(layer, n, d, ci.ptr, co.ptr, aux, s, &e, nullptr, in2, out2);
+    if (rc == LIC_OK && co.copied && hipMemcpyAsync(out, co.ptr, bo, hipMemcpyDeviceToDevice, s) != hipSuccess) {
+        rc = LIC_E_HIP;
+        e = "copy of a layer's output";
+    }
+    he = rc == LIC_OK || ci.copied || co.copied ? hipStreamSynchronize(s) : hipSuccess;
     if (rc != LIC_OK) return fail(c, rc, e);
-    hipError_t he = hipStreamSynchronize(c->layer_stream);
     if (he != hipSuccess) return fail(c, LIC_E_HIP, hipGetErrorString(he));
     return LIC_OK;
 }
