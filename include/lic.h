@@ -302,14 +302,36 @@ int codec_time_layers(codec_t* c, uint32_t mask);
 
 /* Which kernel a layer launches for one H x W frame (nothing is launched):
  * *form = the operand form of its GEMM (LIC_FORM_*), *ksplit = the number of
- * waves that split its K loop (1: one wave per pixel tile).  The choice
- * depends on the codec's precision and the frame size only. */
+ * waves that split its K loop (1: one wave per pixel tile).  Both depend on
+ * the codec's precision and the frame size only, and with them the sums; the
+ * kernel and its tile, which change no sum, also on the number of frames. */
 enum { LIC_FORM_F32 = 0,     /* FP32 operands on the FP32 matrix cores */
        LIC_FORM_BF16 = 1,    /* bf16 operands */
        LIC_FORM_FP8 = 2,     /* OCP e4m3 operands, per-row weight scales */
        LIC_FORM_F32X = 3 };  /* FP32 operands as three exact bf16 parts: six
                                 bf16 products per FP32 product, FP32 sums */
 int codec_layer_kernel(codec_t* c, int layer, int H, int W, int* form, int* ksplit);
+/* The whole choice, for n frames, of a model with these parameters (host
+ * arithmetic: needs neither a codec nor a device; for tests).  route receives
+ * up to max of the LIC_ROUTE_FIELDS numbers.  Fails as the launch would
+ * (LIC_E_ARG: no kernel for these widths). */
+enum { LIC_ROUTE_KERNEL = 0, /* LIC_KERNEL_* */
+       LIC_ROUTE_FORM,       /* LIC_FORM_* */
+       LIC_ROUTE_KSPLIT,     /* K slots */
+       LIC_ROUTE_MT, LIC_ROUTE_NT,   /* a wave's tile: rows / 16, pixels / 16 (split: of the sums) */
+       LIC_ROUTE_WAVES,      /* of a block */
+       LIC_ROUTE_TW,         /* window kernel: columns of a tile */
+       LIC_ROUTE_BLOCKS,     /* of the direct, staged and split kernels */
+       LIC_ROUTE_FIELDS };
+enum { LIC_KERNEL_DIRECT = 0,    /* operands gathered from memory (conv_kernels.hip) */
+       LIC_KERNEL_STAGED = 1,    /* both operands staged in LDS (gdn_kernels.hip) */
+       LIC_KERNEL_WINDOW = 2,    /* a tile's pixels and halo in LDS (window_kernels.hip) */
+       LIC_KERNEL_SPLIT = 3,     /* split K (split_kernels.hip) */
+       LIC_KERNEL_TWO_PASS = 4,  /* split K, then the normalisation in place */
+       LIC_KERNEL_IMAGE = 5,     /* g_a's first layer (image_kernels.hip) */
+       LIC_KERNEL_RGB = 6 };     /* g_s's output layer (rgb_kernels.hip) */
+int lic_layer_route(int kind, int N, int M, int precision, int layer, int n, int H, int W,
+                    int32_t* route, int max);
 int codec_layer_time(codec_t* c, int layer, double* total_ms, long* launches);
 
 /* Entropy tables the codec built at create (host copies, for checking):

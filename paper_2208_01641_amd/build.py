@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "liblic.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 HIP_SOURCES = ["conv_kernels.hip", "gdn_kernels.hip", "window_kernels.hip", "split_kernels.hip", "rgb_kernels.hip", "image_kernels.hip", "distill_kernels.hip", "context_kernels.hip"]
-CPP_SOURCES = ["entropy.cpp", "packing.cpp", "model.cpp", "pipeline.cpp", "server.cpp", "api.cpp", "distill.cpp"]
+CPP_SOURCES = ["entropy.cpp", "packing.cpp", "model.cpp", "dispatch.cpp", "pipeline.cpp", "server.cpp", "api.cpp", "distill.cpp"]
 
 HIPCC = [os.path.join(ROCM, "bin", "hipcc"), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

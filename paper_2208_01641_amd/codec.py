@@ -260,6 +260,20 @@ class Codec:
         return buf[:n].copy()
 
 
+KERNELS = ("direct", "staged", "window", "split", "two_pass", "image", "rgb")
+
+
+def layer_route(layer, n, H, W, kind=1, N=128, M=192, precision=0) -> dict:
+    """The kernel and tile a layer of such a model takes at n frames of H x W
+    (host arithmetic; LicError where no kernel is written for the widths)."""
+    v = (ctypes.c_int32 * 8)()
+    rc = lib.lic_layer_route(kind, N, M, precision, _lib.LAYER_ID[layer], n, H, W, v, 8)
+    if rc != 0:
+        raise LicError(rc, "lic_layer_route")
+    return {"kernel": KERNELS[v[0]], "form": Codec.FORMS[v[1]], "ksplit": v[2], "mt": v[3], "nt": v[4], "waves": v[5],
+            "tw": v[6], "blocks": v[7]}
+
+
 # ---------------------------------------------------------------- host coder
 def rans_encode(sym, tab, freq) -> bytes:
     sym = np.ascontiguousarray(sym, np.uint8).ravel()

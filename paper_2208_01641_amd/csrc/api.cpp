@@ -420,6 +420,24 @@ int codec_layer_kernel(codec_t* c, int layer, int H, int W, int* form, int* kspl
     return LIC_OK;
 }
 
+int lic_layer_route(int kind, int N, int M, int precision, int layer, int n, int H, int W, int32_t* route, int max)
+{
+    if (!route || max < 0) return LIC_E_ARG;
+    if (kind < 0 || kind > 2 || N < 16 || M < 16 || N > 4096 || M > 4096 || N % 16 != 0 || M % 16 != 0) return LIC_E_ARG;
+    if (precision < 0 || precision > 2 || layer < 0 || layer >= LIC_NUM_LAYERS) return LIC_E_ARG;
+    if (n < 1 || H < 1 || W < 1 || H > 65535 || W > 65535) return LIC_E_ARG;
+    lic::ConvRoute r;
+    std::string e;
+    const int rc = lic::layer_route(kind, N, M, precision, layer, n, H, W, &r, &e);
+    if (rc != LIC_OK) return rc;
+    const bool sp = r.kernel == lic::ConvRoute::SPLIT || r.kernel == lic::ConvRoute::TWO_PASS;
+    const int32_t v[LIC_ROUTE_FIELDS] = {(int32_t)r.kernel, r.key.dt, r.key.ksplit, sp ? r.split.mt : r.key.mt,
+                                         sp ? r.split.nt : r.key.nt, sp ? r.split.rg * r.split.ks : r.key.waves,
+                                         r.tw, (int32_t)r.nblocks};
+    for (int i = 0; i < std::min(max, (int)LIC_ROUTE_FIELDS); ++i) route[i] = v[i];
+    return LIC_OK;
+}
+
 int codec_time_layers(codec_t* c, uint32_t mask)
 {
     if (!c) return LIC_E_ARG;

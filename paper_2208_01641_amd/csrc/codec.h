@@ -71,6 +71,32 @@ struct FrameDims {
           Hy(Hp / 16), Wy(Wp / 16), Hz(Hp / 64), Wz(Wp / 64) {}
 };
 
+// Grids of a layer: input, output positions of the GEMM, output.
+Geo layer_geo(int layer, const FrameDims& d);
+
+// A layer of a model kind: name in the weight blob, loader, epilogue, transposed
+// or not, kernel size.
+struct LayerSpec {
+    int id;
+    const char* name;
+    int ld, ep;
+    bool deconv;
+    int k;
+    int cb = -1;           // context model: the checkerboard set the layer is evaluated on
+};
+std::vector<LayerSpec> layer_specs(int kind);
+
+// Its operand form in a precision, and what it stores.
+struct LayerForm {
+    int dt;
+    bool out_e4m3, out_bf16;
+};
+LayerForm layer_form(const LayerSpec& sp, int precision);
+// What the kernel choice needs of it, with ci input and co output channels.
+ConvShape layer_shape(const LayerSpec& sp, const LayerForm& f, int ci, int co);
+// The route of a layer of a kind / N / M / precision model at n frames of H x W.
+int layer_route(int kind, int N, int M, int precision, int layer, int n, int H, int W, ConvRoute* r, std::string* errp);
+
 // ------------------------------------------------------------- pipeline
 struct Codec;
 
@@ -349,7 +375,6 @@ struct Codec {
     // model
     int load(const void* blob, size_t len);
     int build_layers(const std::map<std::string, std::pair<std::vector<int>, std::vector<double>>>& P);
-    Geo geo(int layer, const FrameDims& d) const;
     // Bytes of a layer's input, output and aux tensors for n frames of d
     // (codec_run_layer's buffers; 0 where the layer takes none).
     void layer_bytes(int layer, int n, const FrameDims& d, size_t* in, size_t* out, size_t* aux) const;

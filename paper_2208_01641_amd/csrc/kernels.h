@@ -73,11 +73,21 @@ struct ConvShape {
     int halo1 = 0;     // stride-1 grid, every tap within one pixel (halo-tile loader allowed)
 };
 
-// Picks the tile configuration (split-K for small grids) from policy_pixels
-// (the pixel grid of one image, so that results do not depend on the batch),
-// sets a.ncog and launches over the a.n x a.Hg x a.Wg grid.  Returns a
-// lic_status; *errp names the failure.
-// With chosen non-null nothing is launched: the configuration is stored there.
+// The kernel of a layer over an a.n x a.Hg x a.Wg grid.
+struct ConvRoute {
+    enum Kernel { DIRECT, STAGED, WINDOW, SPLIT, TWO_PASS, IMAGE, RGB } kernel;
+    KernelKey key;         // operand form and K slots; of the direct and staged kernels all of it
+    SplitKey split;        // SPLIT, TWO_PASS: the tile (TWO_PASS: of the sums)
+    int ncog, tw;          // blocks along the output channels; WINDOW: columns of a tile
+    long nblocks;          // (IMAGE, RGB, WINDOW: their launches count their own)
+};
+// Host arithmetic only, on the grids and strides in a (its pointers are not
+// looked at).  What fixes the order of the sums, the operand form and the K
+// slots, comes from policy_pixels, the pixel grid of one image, so that results
+// do not depend on the batch.  Returns a lic_status; *errp names the failure.
+int choose_route(const ConvShape& L, const ConvArgs& a, long policy_pixels, ConvRoute* r, std::string* errp);
+// Chooses and launches (sets a.ncog, a.tw).  With chosen non-null nothing is
+// launched: the route's key is stored there.
 int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipStream_t s, std::string* errp,
                        KernelKey* chosen = nullptr);
 

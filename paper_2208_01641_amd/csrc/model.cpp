@@ -314,18 +314,77 @@ long blob_tables(const void* blob, size_t len, int which, uint32_t* freq, size_t
     return (long)src.size();
 }
 
-namespace {
+std::vector<LayerSpec> layer_specs(int kind)
+{
+    std::vector<LayerSpec> specs = {
+        {LIC_GA0, "ga0", LD_RGB, EP_GDN, false, 5}, {LIC_GA1, "ga1", LD_F32, EP_GDN, false, 5},
+        {LIC_GA2, "ga2", LD_F32, EP_GDN, false, 5}, {LIC_GA3, "ga3", LD_F32, EP_QUANT, false, 5},
+        {LIC_GS0, "gs0", LD_I8, EP_IGDN, true, 5},  {LIC_GS1, "gs1", LD_F32, EP_IGDN, true, 5},
+        {LIC_GS2, "gs2", LD_F32, EP_IGDN, true, 5}, {LIC_GS3, "gs3", LD_F32, EP_RGB, true, 5},
+    };
+    if (kind >= 1) {
+        // the context model's h_a sees y (the means need its signs), its h_s
+        // ends in psi (2M channels, no activation) and g_s starts from the
+        // float y_hat = sym + mean
+        std::vector<LayerSpec> hyper = {
+            {LIC_HA0, "ha0", kind == 1 ? LD_F32_ABS : LD_F32, EP_RELU, false, 3},
+            {LIC_HA1, "ha1", LD_F32, EP_RELU, false, 5},
+            {LIC_HA2, "ha2", LD_F32, EP_QUANT, false, 5},    {LIC_HS0, "hs0", LD_I8, EP_RELU, true, 5},
+            {LIC_HS1, "hs1", LD_F32, EP_RELU, true, 5},
+            {LIC_HS2, "hs2", LD_F32, kind == 1 ? EP_INDEX : EP_NONE, false, 3},
+        };
+        specs.insert(specs.end(), hyper.begin(), hyper.end());
+    }
+    if (kind == 2) {
+        specs[4].ld = LD_F32;                            // gs0
+        std::vector<LayerSpec> ctx = {
+            {LIC_CX, "cx", LD_F32, EP_NONE, false, 5, 1},
+            {LIC_EP0A, "ep0", LD_F32, EP_RELU, false, 1, 0},   {LIC_EP1A, "ep1", LD_F32, EP_RELU, false, 1, 0},
+            {LIC_EP2A, "ep2", LD_F32, EP_MSCALE, false, 1, 0}, {LIC_EP0N, "ep0", LD_F32, EP_RELU, false, 1, 1},
+            {LIC_EP1N, "ep1", LD_F32, EP_RELU, false, 1, 1},   {LIC_EP2N, "ep2", LD_F32, EP_MSCALE, false, 1, 1},
+        };
+        specs.insert(specs.end(), ctx.begin(), ctx.end());
+    }
+    return specs;
+}
 
-struct Spec {
-    int id;
-    const char* name;
-    int ld, ep;
-    bool deconv;
-    int k;
-    int cb = -1;       // context model: the checkerboard set the layer is evaluated on
-};
+LayerForm layer_form(const LayerSpec& sp, int precision)
+{
+    LayerForm f{DT_F32, false, false};
+    // bf16 operands for the analysis / synthesis transforms in the BF16
+    // form; h_a and h_s always run in FP32 (fixed-order scale index)
+    const bool is_gags = sp.id <= LIC_GA3 || (sp.id >= LIC_GS0 && sp.id <= LIC_GS3);
+    if (is_gags) f.dt = precision == LIC_PREC_BF16 ? DT_BF16 : precision == LIC_PREC_FP8 ? DT_FP8 : DT_F32;
+    // the e4m3 form's image layer: bf16 operands (a K of 75 is one
+    // chunk; pixel values keep 8 bits), e4m3 activations out; so does
+    // g_s's first layer (its symbol loader's conversion to e4m3 does not
+    // fit two waves per SIMD, the bf16 kernel does; the context model's
+    // y_hat = sym + mean arrives as bf16 anyway)
+    f.out_e4m3 = f.dt == DT_FP8 && (sp.ld == LD_RGB || sp.id == LIC_GS0);
+    if (f.out_e4m3) f.dt = DT_BF16;
+    // and its output layer too (bf16 halo tiles: the 3 output channels
+    // make a K chunk of 128 (tap, channel) pairs a poor fit), fed by a
+    // last GDN layer that stores bf16
+    if (f.dt == DT_FP8 && sp.id == LIC_GS3) f.dt = DT_BF16;
+    f.out_bf16 = f.dt == DT_FP8 && sp.id == LIC_GS2;
+    return f;
+}
 
-}  // namespace
+ConvShape layer_shape(const LayerSpec& sp, const LayerForm& f, int ci, int co)
+{
+    const bool rows = sp.ep == EP_RGB;                   // all phases as GEMM rows
+    ConvShape L{};
+    L.tag = sp.id;
+    L.ld = sp.ld;
+    L.ep = sp.ep;
+    L.dt = f.dt;
+    L.cin = sp.ld == LD_RGB ? 96 : ci;                   // the image: 75 (tap, channel) pairs in whole K chunks
+    L.cop = rows ? 16 : co;
+    L.nphase = sp.cb >= 0 ? 2 : sp.deconv && !rows ? 4 : 1;
+    // taps within one pixel of a stride-1 grid: a stride-2 transposed 5 x 5, 3 x 3, 1 x 1
+    L.halo1 = sp.ld != LD_RGB && (sp.deconv || sp.k <= 3) ? 1 : 0;
+    return L;
+}
 
 int Codec::upload_rscale(LayerGPU& L)
 {
@@ -442,37 +501,7 @@ int Codec::build_layers(const ParamMap& P)
     if (!thr.empty()) HIP_TRY(hipMemcpy(d_thr, thr.data(), 63 * sizeof(float), hipMemcpyHostToDevice));
     (void)C;
 
-    std::vector<Spec> specs = {
-        {LIC_GA0, "ga0", LD_RGB, EP_GDN, false, 5}, {LIC_GA1, "ga1", LD_F32, EP_GDN, false, 5},
-        {LIC_GA2, "ga2", LD_F32, EP_GDN, false, 5}, {LIC_GA3, "ga3", LD_F32, EP_QUANT, false, 5},
-        {LIC_GS0, "gs0", LD_I8, EP_IGDN, true, 5},  {LIC_GS1, "gs1", LD_F32, EP_IGDN, true, 5},
-        {LIC_GS2, "gs2", LD_F32, EP_IGDN, true, 5}, {LIC_GS3, "gs3", LD_F32, EP_RGB, true, 5},
-    };
-    if (kind >= 1) {
-        // the context model's h_a sees y (the means need its signs), its h_s
-        // ends in psi (2M channels, no activation) and g_s starts from the
-        // float y_hat = sym + mean
-        std::vector<Spec> hyper = {
-            {LIC_HA0, "ha0", kind == 1 ? LD_F32_ABS : LD_F32, EP_RELU, false, 3},
-            {LIC_HA1, "ha1", LD_F32, EP_RELU, false, 5},
-            {LIC_HA2, "ha2", LD_F32, EP_QUANT, false, 5},    {LIC_HS0, "hs0", LD_I8, EP_RELU, true, 5},
-            {LIC_HS1, "hs1", LD_F32, EP_RELU, true, 5},
-            {LIC_HS2, "hs2", LD_F32, kind == 1 ? EP_INDEX : EP_NONE, false, 3},
-        };
-        specs.insert(specs.end(), hyper.begin(), hyper.end());
-    }
-    if (kind == 2) {
-        specs[4].ld = LD_F32;                            // gs0
-        std::vector<Spec> ctx = {
-            {LIC_CX, "cx", LD_F32, EP_NONE, false, 5, 1},
-            {LIC_EP0A, "ep0", LD_F32, EP_RELU, false, 1, 0},   {LIC_EP1A, "ep1", LD_F32, EP_RELU, false, 1, 0},
-            {LIC_EP2A, "ep2", LD_F32, EP_MSCALE, false, 1, 0}, {LIC_EP0N, "ep0", LD_F32, EP_RELU, false, 1, 1},
-            {LIC_EP1N, "ep1", LD_F32, EP_RELU, false, 1, 1},   {LIC_EP2N, "ep2", LD_F32, EP_MSCALE, false, 1, 1},
-        };
-        specs.insert(specs.end(), ctx.begin(), ctx.end());
-    }
-
-    for (const Spec& sp : specs) {
+    for (const LayerSpec& sp : layer_specs(kind)) {
         LayerGPU& L = layers[sp.id];
         auto wit = P.find(std::string(sp.name) + ".w");
         auto bit = P.find(std::string(sp.name) + ".b");
@@ -495,39 +524,34 @@ int Codec::build_layers(const ParamMap& P)
         L.deconv = sp.deconv;
         L.co = co;
         L.rows = sp.ep == EP_RGB;
-        // bf16 operands for the analysis / synthesis transforms in the BF16
-        // form; h_a and h_s always run in FP32 (fixed-order scale index)
-        const bool is_gags = sp.id <= LIC_GA3 || (sp.id >= LIC_GS0 && sp.id <= LIC_GS3);
-        L.dt = !is_gags ? DT_F32 : cfg.precision == LIC_PREC_BF16 ? DT_BF16 : cfg.precision == LIC_PREC_FP8 ? DT_FP8 : DT_F32;
-        // the e4m3 form's image layer: bf16 operands (a K of 75 is one
-        // chunk; pixel values keep 8 bits), e4m3 activations out; so does
-        // g_s's first layer (its symbol loader's conversion to e4m3 does not
-        // fit two waves per SIMD, the bf16 kernel does; the context model's
-        // y_hat = sym + mean arrives as bf16 anyway)
-        L.out_e4m3 = L.dt == DT_FP8 && (sp.ld == LD_RGB || sp.id == LIC_GS0);
-        if (L.out_e4m3) L.dt = DT_BF16;
-        // and its output layer too (bf16 halo tiles: the 3 output channels
-        // make a K chunk of 128 (tap, channel) pairs a poor fit), fed by a
-        // last GDN layer that stores bf16
-        if (L.dt == DT_FP8 && sp.id == LIC_GS3) L.dt = DT_BF16;
-        L.out_bf16 = L.dt == DT_FP8 && sp.id == LIC_GS2;
-        // 75 (tap, channel) pairs in whole K chunks
-        const int krgb = L.dt == DT_FP8 ? 128 : 96;
-        L.cin = sp.ld == LD_RGB ? krgb : ci;
-        L.cop = L.rows ? 16 : co;
+        const LayerForm form = layer_form(sp, cfg.precision);
+        const ConvShape shape = layer_shape(sp, form, ci, co);
+        L.dt = form.dt;
+        L.out_e4m3 = form.out_e4m3;
+        L.out_bf16 = form.out_bf16;
+        L.cin = shape.cin;
+        L.cop = shape.cop;
+        L.nphase = shape.nphase;
+        L.halo1 = shape.halo1 != 0;
         if (sp.ld == LD_RGB && ci != 3) { err = "ga0 must take 3 channels"; return LIC_E_MODEL; }
         if (!L.rows && co % 16 != 0) { err = std::string("channels must be multiples of 16: ") + sp.name; return LIC_E_MODEL; }
         if (L.rows && co != 3) { err = "gs3 must produce 3 channels"; return LIC_E_MODEL; }
         // packed GEMM operands as index maps into the PyTorch-layout weights
         PackMap pm;
         if (sp.cb >= 0) pm = pack_map_checkerboard(ci, co, k, sp.cb, sp.ep == EP_MSCALE);
-        else if (sp.ld == LD_RGB) pm = pack_map(PK_IMG, 3, co, k, 2, k / 2, false, krgb);
+        else if (sp.ld == LD_RGB) pm = pack_map(PK_IMG, 3, co, k, 2, k / 2, false, L.cin);
         else if (!sp.deconv) pm = pack_map(PK_CONV, ci, co, k, 1, k / 2, false);
         else if (!L.rows) pm = pack_map(PK_DECONV, ci, co, k, 2, k / 2, true);
         else pm = pack_map(PK_ROWS, ci, co, k, 2, k / 2, true);
-        if (pm.cin != L.cin || pm.cop != L.cop) { err = std::string("packing mismatch in ") + sp.name; return LIC_E_MODEL; }
         std::vector<PhaseDesc> ph = pm.ph;
-        L.nphase = (int)ph.size();
+        bool halo1 = sp.ld != LD_RGB;
+        for (const PhaseDesc& d : ph)
+            for (int t = 0; t < d.ntaps; ++t)
+                if (d.dy[t] < -1 || d.dy[t] > 1 || d.dx[t] < -1 || d.dx[t] > 1) halo1 = false;
+        if (pm.cin != L.cin || pm.cop != L.cop || (int)ph.size() != L.nphase || halo1 != L.halo1) {
+            err = std::string("packing mismatch in ") + sp.name;
+            return LIC_E_MODEL;
+        }
 
         const size_t total = pm.idx.size();
         const size_t esz = L.dt == DT_BF16 ? 2 : L.dt == DT_FP8 ? 1 : 4;
@@ -634,10 +658,6 @@ int Codec::build_layers(const ParamMap& P)
         }
         HIP_TRY(hipMemcpy(L.d_ph, ph.data(), ph.size() * sizeof(PhaseDesc), hipMemcpyHostToDevice));
         L.host_ph = ph;
-        L.halo1 = sp.ld != LD_RGB;
-        for (const PhaseDesc& d : ph)
-            for (int t = 0; t < d.ntaps; ++t)
-                if (d.dy[t] < -1 || d.dy[t] > 1 || d.dx[t] < -1 || d.dx[t] > 1) L.halo1 = false;
         std::vector<float> bias(L.cop, 0.0f);
         for (int r = 0; r < L.cop; ++r)
             if (pm.bias_idx[r] >= 0) bias[r] = (float)b[pm.bias_idx[r]];
@@ -684,7 +704,7 @@ int Codec::build_layers(const ParamMap& P)
     return LIC_OK;
 }
 
-Geo Codec::geo(int id, const FrameDims& d) const
+Geo layer_geo(int id, const FrameDims& d)
 {
     const int Hp = d.Hp, Wp = d.Wp, Hy = d.Hy, Wy = d.Wy, Hz = d.Hz, Wz = d.Wz;
     switch (id) {
@@ -718,7 +738,7 @@ static size_t act_bytes(const LayerGPU& L)
 
 void Codec::layer_bytes(int id, int n, const FrameDims& d, size_t* in, size_t* out, size_t* aux) const
 {
-    const Geo g = geo(id, d);
+    const Geo g = layer_geo(id, d);
     const size_t nn = (size_t)n;
     const size_t img = nn * 3 * d.H * d.W;
     const size_t px_in = nn * g.Hin * g.Win, px_out = nn * g.Hout * g.Wout;
@@ -772,7 +792,7 @@ int Codec::launch_layer(int id, int n, const FrameDims& d, const void* in, void*
 {
     if (id < 0 || id >= LIC_NUM_LAYERS || !layers[id].present) { *errp = "layer not present in this model"; return LIC_E_ARG; }
     const LayerGPU& L = layers[id];
-    const Geo g = geo(id, d);
+    const Geo g = layer_geo(id, d);
     ConvArgs a{};
     a.in = in;
     a.out = out;
@@ -831,211 +851,40 @@ int Codec::launch_layer(int id, int n, const FrameDims& d, const void* in, void*
     return launch_conv_policy(shape, a, (long)g.Hg * g.Wg, s, errp, chosen);
 }
 
-// The widths that the codec's kernels are written for.  Some of them take any
-// number of input channels at run time (conv_split), and would read and write
-// past their tiles at others.
-static bool codec_widths(const ConvShape& L)
+int layer_route(int kind, int N, int M, int precision, int id, int n, int H, int W, ConvRoute* r, std::string* errp)
 {
-    const int ci = L.cin, co = L.cop;
-    switch (L.tag) {
-    case LIC_GA0: return ci == 96 && (co == 128 || co == 192);
-    case LIC_GA1: case LIC_GA2: case LIC_GS1: case LIC_GS2: return ci == co && (co == 128 || co == 192);
-    case LIC_GS0: return (ci == 192 && co == 128) || (ci == 320 && co == 192 && L.ld == LD_I8);
-    case LIC_GA3: case LIC_HA1: case LIC_HA2: case LIC_HS0: case LIC_HS1: case LIC_GS3: return ci == 128 || ci == 192;
-    case LIC_HA0: return ci == 192 || (ci == 320 && L.ld == LD_F32_ABS);
-    case LIC_HS2: return ci == 128 || (ci == 192 && L.ep == EP_INDEX);
-    case LIC_CX: return ci == 192;
-    case LIC_EP0A: case LIC_EP0N: return ci == 768;
-    case LIC_EP1A: case LIC_EP1N: return ci == 640;
-    case LIC_EP2A: case LIC_EP2N: return ci == 512;
+    for (const LayerSpec& sp : layer_specs(kind)) {
+        if (sp.id != id) continue;
+        int ci = N, co = N;
+        switch (id) {
+        case LIC_GA0: ci = 3; break;
+        case LIC_GA3: co = M; break;
+        case LIC_HA0: case LIC_GS0: ci = M; break;
+        case LIC_GS3: co = 3; break;
+        case LIC_HS2: co = kind == 2 ? 2 * M : M; break;
+        case LIC_CX: ci = M; co = 2 * M; break;
+        case LIC_EP0A: case LIC_EP0N: ci = 4 * M; co = 640; break;
+        case LIC_EP1A: case LIC_EP1N: ci = 640; co = 512; break;
+        case LIC_EP2A: case LIC_EP2N: ci = 512; co = 2 * M; break;
+        }
+        const Geo g = layer_geo(id, FrameDims(H, W));
+        ConvShape L = layer_shape(sp, layer_form(sp, precision), ci, co);
+        L.halo1 = L.halo1 && g.s_in == 1 ? 1 : 0;
+        ConvArgs a{};
+        a.n = n;
+        a.Hin = g.Hin;
+        a.Win = g.Win;
+        a.Hg = g.Hg;
+        a.Wg = g.Wg;
+        a.s_in = g.s_in;
+        a.s_out = g.s_out;
+        a.kk = sp.k;
+        a.Co = co;
+        a.co_ld = kind == 2 && (id == LIC_HS2 || id == LIC_CX) ? 4 * M : 0;
+        return choose_route(L, a, (long)g.Hg * g.Wg, r, errp);
     }
-    return true;                                        // the distilled network: by its kernels' keys
-}
-
-int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipStream_t s, std::string* errp,
-                       KernelKey* chosen)
-{
-    KernelKey key{L.tag, L.cin, 0, 0, 0, 1, L.ld, L.ep, L.dt};
-    const long pixels = (long)a.n * a.Hg * a.Wg;
-    bool staged = false, rgb = false, image = false, window = false;
-    if (L.ep == EP_GDN || L.ep == EP_IGDN) {
-        key.mt = L.cop / 16;
-        key.nt = key.mt <= 8 ? 2 : 1;
-        key.waves = 4;
-        a.ncog = 1;
-        // Fewer than one wave per SIMD (1024 on the chip) from the pixel
-        // grid of one image: split K over the 4 waves of a block instead,
-        // unless 16-pixel groups give at least half a wave per SIMD (128
-        // channels; of the e4m3 layers only GA2).  The choice sets the order
-        // of the sums, so it looks at one image only and not at the batch.
-        const long img_waves = (policy_pixels + 16 * key.nt - 1) / (16 * key.nt) * L.nphase;
-        const long waves1 = (policy_pixels + 15) / 16 * L.nphase;
-        if (L.ld != LD_RGB && img_waves < 1024 &&
-            !(key.mt == 8 && waves1 >= 512 && (L.dt != DT_FP8 || L.tag == LIC_GA2)))
-            key.ksplit = 4;
-        if (L.ld == LD_RGB && a.ws && L.nphase == 1 && a.kk == 5 && a.s_in == 2 && a.Wg % 32 == 0 &&
-            image_available(L.cop, key.dt == DT_F32 ? DT_F32X : key.dt)) {
-            if (key.dt == DT_F32) key.dt = DT_F32X;
-            image = true;
-        }
-        if (L.ld != LD_RGB && key.ksplit == 1 && a.wt) {
-            // Both operands staged in LDS, one or two 16-pixel tiles per wave
-            // (the same sums either way).
-            KernelKey ks = key;
-            if (ks.dt == DT_F32) ks.dt = DT_F32X;
-            ks.waves = ks.dt == DT_F32X && ks.mt == 12 ? 8 : 4;
-            ks.nt = (pixels + 31) / 32 * L.nphase >= 1024 ? 2 : 1;
-            if (!gdn_available(ks)) ks.nt = 1;
-            if (gdn_available(ks)) {
-                key = ks;
-                staged = true;
-            }
-            // Large grids of g_s: a tile's pixels and their halo in LDS (again the
-            // same sums), 256 pixels and a phase per block.  16 x 16 or 8 x 32 pixels, whichever
-            // leaves fewer tiles.  Measured against the above (us; blocks in
-            // brackets): bf16 30 -> 33 [240], 52 -> 42 [416], 53 -> 43 [448], 104 -> 77
-            // [960]; FP32 86 -> 91 [240], 160 -> 138 [416], 350 -> 297 [960]; e4m3 22
-            // -> 23 [240], 38 -> 31 [416], 77 -> 56 [960]; 192 channels bf16 54 -> 55
-            // [240], 101 -> 87 [448], e4m3 41 -> 36 [240], 74 -> 59 [448].  Just above
-            // 512 blocks, where those kernels just fill the chip twice, they stay
-            // ahead (FP32 176 against 183, e4m3 43 against 46 [540]).
-            if (staged && L.halo1 && L.ep == EP_IGDN && L.ld == LD_F32 && window_available(L.tag, L.cin, L.cop, key.dt)) {
-                auto blocks = [&](int tw) {
-                    const int th = kWindowPixels / tw;
-                    return (long)a.n * ((a.Hg + th - 1) / th) * ((a.Wg + tw - 1) / tw) * L.nphase;
-                };
-                a.tw = blocks(32) < blocks(16) ? 32 : 16;
-                const long nb = blocks(a.tw);
-                const bool twice = nb > 512 && (pixels + 127) / 128 * L.nphase <= 1024;
-                window = nb >= (L.cop == 192 && key.dt == DT_FP8 ? 200 : 400) && !twice;
-            }
-        }
-    } else if (L.ep == EP_RGB) {
-        // every row of the transposed convolution to 3 channels in one wave;
-        // halo tiles staged per block when the taps allow
-        key.mt = L.cop / 16;
-        key.nt = 4;
-        key.waves = 4;
-        a.ncog = 1;
-        if (L.halo1 && L.ld == LD_F32 && a.ws && a.s_out == 2 && L.cop == 16 && a.Hg % 8 == 0 && a.Wg % 32 == 0 &&
-            rgb_available(L.cin, L.dt)) {
-            key.ld = LD_TILE;
-            rgb = true;
-        } else if (L.halo1 && L.ld == LD_F32) {
-            KernelKey kt = key;
-            kt.ld = LD_TILE;
-            if (kernel_available(kt)) key = kt;
-        }
-    } else {
-        // 64-channel x 32-pixel wave tiles; when the grid of one image gives
-        // fewer than 2 waves per SIMD, split K over 4 or 8 waves of a block;
-        // grids of fewer than 128 such tiles (the 24 x 40 and 12 x 20 hyper
-        // layers of a 720p frame) take 16 x 16 tiles (split 8) instead, for
-        // 8 times the blocks (measured: h_a's second layer 44 -> 30 us, h_s's
-        // first 22 -> 16 us; the 48 x 80 layers are slower that way).  The
-        // choice depends on the per-image size only, so a frame gives the
-        // same bits alone or in a batch (split-K changes the summation order).
-        const long tiles_big = ((policy_pixels + 31) / 32) * L.nphase * (L.cop / 64);
-        key.mt = 4; key.nt = 2;
-        if (L.cop % 64 != 0 || tiles_big < 128) {
-            key.mt = 1; key.nt = 1; key.waves = 8; key.ksplit = 8;
-        } else if (tiles_big >= 2048) {
-            key.waves = 4; key.ksplit = 1;
-        } else if (tiles_big * 4 >= 2048) {
-            key.waves = 4; key.ksplit = 4;
-        } else {
-            key.waves = 8; key.ksplit = 8;
-        }
-        a.ncog = L.cop / (16 * key.mt);
-    }
-    // whole-frame GDN layers of the FP32 form run on split-FP32 operands
-    if (key.dt == DT_F32 && key.ksplit == 1 && a.wx && (L.ep == EP_GDN || L.ep == EP_IGDN)) {
-        KernelKey kx = key;
-        kx.dt = DT_F32X;
-        if (kernel_available(kx)) {
-            key = kx;
-            a.w = a.wx;
-        }
-    }
-    // Split K: the K slots are fixed by the rule above, the tile of a block is
-    // free (the same sums whatever it is): the largest that still gives the
-    // chip enough blocks.  Measured at 720p (us; blocks in brackets): g_a's last
-    // layer 64 x 32 62 [360], 64 x 16 53 [720], 32 x 16 58 [1440]; the same at
-    // 470 x 834 36 [168], 35 [336], 31 [672]; h_a's second 31 [60], 19 [120], 14
-    // [240], 16 x 16 15 [480]; its third 31, 18, 12 [60], 10 [120]; bf16 g_a's
-    // last 18 [360], 21 [720].
-    // Reduced-precision GDN layers that the rule above gives four K slots, on grids
-    // (of the whole batch) of enough blocks for the staged kernel: its waves keep the four
-    // sums side by side, so a block's weights serve 64 pixels instead of 16 or 32.
-    // Measured (layer call, us; blocks in brackets): e4m3 GA1 28 -> 34 [64], 37 -> 35 [96],
-    // 45 -> 35 [160], 54 -> 36 [240], GS1 43 -> 32 [384]; bf16 GA1 33 -> 49 [64], 41 -> 49
-    // [96], 45 -> 45 [160], GA2 54 -> 51 [192]; 192 channels e4m3 GA2 80 -> 50 [240], bf16
-    // GA1 66 -> 70 [96], 93 -> 73 [160], GA2 122 -> 75 [240].
-    if (key.ksplit == 4 && (L.ep == EP_GDN || L.ep == EP_IGDN) && a.wt) {
-        KernelKey k4 = key;
-        k4.nt = 1;
-        k4.waves = 4;
-        if (gdn_available(k4) && (pixels + 63) / 64 * L.nphase >= (L.dt == DT_FP8 ? 96 : 160)) {
-            key = k4;
-            staged = true;
-        }
-    }
-    SplitKey sk{};
-    bool two_pass = false;
-    if (key.ksplit > 1 && a.ws && !staged) {
-        const bool gdn = L.ep == EP_GDN || L.ep == EP_IGDN;
-        sk = SplitKey{4, 1, gdn ? key.mt / 4 : 1, key.ksplit, L.ld, L.ep, L.dt};
-        auto blocks = [&](int mt, int nt) { return (pixels + 16 * nt - 1) / (16 * nt) * L.nphase * (gdn ? 1 : L.cop / (16 * mt)); };
-        if (gdn) {
-            // (FP32; layer call, us, 16- and 32-pixel tiles: GA1 at 256 x 256, four
-            // images, 147 and 143 [512], GS2 at 128 x 128 68 and 68 [512], 115 and 117 [1024])
-            if (blocks(4, 2) >= 512) sk.nt = 2;
-            if (!split_available(sk)) sk.nt = 1;
-        } else if (L.cop % 64 == 0 && blocks(4, 2) >= (L.dt == DT_F32 ? 1024 : 320)) {
-            sk.nt = 2;
-        } else if (L.cop % 64 != 0 || blocks(4, 1) < 448) {
-            sk.mt = L.cop % 32 == 0 && (blocks(2, 1) >= 200 || key.ksplit != 8) ? 2 : 1;
-        }
-        // The smallest FP32 GDN layers leave most of the chip idle in blocks of
-        // all rows: the sums in blocks of 16 or 32 rows instead, then the normalisation in
-        // place by a second launch (layer call, us; blocks of all rows in
-        // brackets): GA2 49 -> 31 [4], 49 -> 31 [16], 49 -> 36 [64], 50 -> 42 [96], 52 ->
-        // 51 [140]; GS1 33 -> 29 [64], 33 -> 34 [144]; 192 channels GA1 83 -> 51 [64], 88 ->
-        // 76 [144], 95 -> 106 [256].  Blocks of 16 rows up to 48: 31 against 35 [16], 37
-        // against 36 [64].
-        const long whole = gdn ? blocks(4, 1) : 0;
-        if (gdn && L.dt == DT_F32 && !a.co_ld && whole <= (L.cop == 128 ? 128 : 160)) {
-            const SplitKey sums{whole <= 48 ? 1 : 2, 1, 1, key.ksplit, L.ld, EP_NONE, DT_F32};
-            if ((L.cop == 128 || L.cop == 192) && split_available(sums)) {
-                sk = sums;
-                two_pass = true;
-            }
-        }
-        if (split_available(sk)) a.ncog = gdn && !two_pass ? 1 : L.cop / (16 * sk.mt);
-        else sk = SplitKey{};
-    }
-    const long per_block = (long)(staged ? key.waves : key.waves / key.ksplit) * key.nt * 16;
-    // halo tiles: one block per key.waves grid rows x 16 key.nt pixels
-    const long tiles = sk.mt ? (pixels + 16 * sk.nt - 1) / (16 * sk.nt)
-                       : key.ld == LD_TILE
-                           ? (long)a.n * ((a.Hg + key.waves - 1) / key.waves) * ((a.Wg + 16 * key.nt - 1) / (16 * key.nt))
-                           : (pixels + per_block - 1) / per_block;
-    const long nblocks = tiles * L.nphase * a.ncog;
-    if (nblocks <= 0 && !chosen) return LIC_OK;
-    if (nblocks > (1L << 30)) { *errp = "launch too large"; return LIC_E_BUDGET; }
-    if (!codec_widths(L) || (!staged && !rgb && !image && !sk.mt && !kernel_available(key))) { *errp = "no kernel instantiated for this layer shape"; return LIC_E_ARG; }
-    if (chosen) {
-        *chosen = key;
-        return LIC_OK;
-    }
-    hipError_t e = window ? launch_window(L.tag, L.cin, L.cop, key.dt, a, s) : image ? launch_image(key.dt, a, s) : rgb ? launch_rgb(L.cin, L.dt, a, s) : staged ? launch_gdn(key, a, (int)nblocks, s)
-                   : sk.mt ? launch_split(sk, a, (int)nblocks, s) : launch_conv(key, a, (int)nblocks, s);
-    if (e == hipSuccess && two_pass) e = launch_gdn_apply(L.cop, L.ep, a, s);
-    if (e != hipSuccess) {
-        *errp = std::string("kernel launch failed: ") + hipGetErrorString(e);
-        return LIC_E_HIP;
-    }
-    return LIC_OK;
+    *errp = "layer not present in this model";
+    return LIC_E_ARG;
 }
 
 }  // namespace lic

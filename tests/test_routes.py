@@ -1,0 +1,110 @@
+"""The choice of kernels, on the CPU: what the GPU tests of each kernel are named
+for is what they run, nothing that fixes a sum depends on the batch, every
+model has a kernel at every size, and other widths have none."""
+import pytest
+
+from paper_2208_01641_amd.codec import LicError, layer_route
+from route_util import GDN, MODELS, routes, tile
+import test_gpu_split
+import test_gpu_staged
+import test_gpu_window
+
+FP32, BF16, FP8 = 0, 1, 2
+
+
+def kernel(prec, layer, N, M, n, H, W):
+    return layer_route(layer, n, H, W, 1, N, M, prec)["kernel"]
+
+
+def test_split_cases():
+    """All but the grids that the staged kernel with four sums takes; the FP32
+    GDN layers of few blocks in two passes."""
+    four = {(BF16, "GA1", 128, 192, 5, 256, 320), (FP8, "GS1", 128, 192, 1, 512, 768), (FP8, "GS1", 192, 320, 5, 256, 320)}
+    two = {(FP32, "GA1", 128, 192, 1, 64, 64), (FP32, "GA2", 128, 192, 1, 64, 128), (FP32, "GA2", 128, 192, 3, 64, 64),
+           (FP32, "GS0", 128, 192, 3, 64, 64), (FP32, "GS2", 128, 192, 1, 64, 128), (FP32, "GA1", 192, 320, 1, 64, 128),
+           (FP32, "GS0", 192, 320, 3, 64, 192)}
+    for c in test_gpu_split.CASES:
+        assert kernel(*c) == ("staged" if c in four else "two_pass" if c in two else "split"), c
+
+
+def test_two_pass_cases():
+    """Alone in two passes, the batch in one (GS0's batch of 11: in blocks of 32 rows instead of 16)."""
+    for layer, N, M, n, H, W, _ in test_gpu_split.TWO_PASS:
+        alone, batch = (layer_route(layer, k, H, W, 1, N, M, FP32) for k in (1, n))
+        assert alone["kernel"] == "two_pass", (layer, N, H, W)
+        assert batch["kernel"] == "split" or tile(batch) != tile(alone), (layer, N, n, H, W)
+
+
+def test_four_sums_cases():
+    """The batch on the staged kernel with four K slots, alone split (e4m3 GS2: both staged)."""
+    for prec, layer, N, M, n, H, W, _ in test_gpu_split.FOUR_SUMS:
+        batch = layer_route(layer, n, H, W, 1, N, M, prec)
+        assert (batch["kernel"], batch["ksplit"]) == ("staged", 4), (prec, layer, n)
+        alone = kernel(prec, layer, N, M, 1, H, W)
+        assert alone == ("staged" if (prec, layer, H) == (FP8, "GS2", 128) else "split"), (prec, layer)
+
+
+def test_staged_cases():
+    for c in test_gpu_staged.CASES:
+        window = c in {(BF16, "GS2", 192, 320, 1, 576, 960), (FP8, "GS2", 192, 320, 1, 576, 960)}
+        assert kernel(*c) == ("window" if window else "staged"), c
+    nts = {(c[0], layer_route(c[1], c[4], c[5], c[6], 1, c[2], c[3], c[0])["nt"]) for c in test_gpu_staged.CASES}
+    assert {(FP32, 1), (FP32, 2), (BF16, 1), (BF16, 2), (FP8, 1), (FP8, 2)} <= nts
+
+
+def test_window_cases():
+    tws = set()
+    for prec, layer, N, M, n, H, W, _ in test_gpu_window.CASES:
+        batch = layer_route(layer, n, H, W, 1, N, M, prec)
+        assert batch["kernel"] == "window" and kernel(prec, layer, N, M, 1, H, W) == "staged", (prec, layer, n, H, W)
+        tws.add(batch["tw"])
+    assert tws == {16, 32}
+
+
+SIZES = [1, 64, 65, 200, 256, 320, 360, 448, 470, 512, 704, 720, 1024, 1080, 1920, 4096, 8192]
+
+
+@pytest.mark.parametrize("kind,N,M,precision,layers", MODELS)
+def test_every_size_has_a_kernel_and_sums_do_not_depend_on_the_batch(kind, N, M, precision, layers):
+    for layer in layers:
+        for H in SIZES:
+            for W in SIZES:
+                alone = layer_route(layer, 1, H, W, kind, N, M, precision)
+                for n in (2, 5, 33):
+                    r = layer_route(layer, n, H, W, kind, N, M, precision)
+                    assert (r["form"], r["ksplit"]) == (alone["form"], alone["ksplit"]), (layer, n, H, W)
+
+
+def test_output_layer_is_fp32():
+    for N, M in ((128, 192), (192, 320)):
+        assert tile(layer_route("GS3", 1, 720, 1280, 1, N, M, FP32))[:3] == ("rgb", "f32", 1)
+
+
+@pytest.mark.parametrize("N,M", [(64, 96), (160, 192), (144, 208), (224, 320), (128, 320), (192, 192), (256, 384)])
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_other_widths_are_refused(N, M, precision):
+    """Layers whose widths are those of a supported model run; the others have no kernel at any size."""
+    fits = {"GA0": N in (128, 192), "GA1": N in (128, 192), "GA2": N in (128, 192), "GS1": N in (128, 192), "GS2": N in (128, 192),
+            "GS0": (M, N) in ((192, 128), (320, 192)), "HA0": M in (192, 320)}
+    for layer in ["GA0", "GA1", "GA2", "GA3", "GS0", "GS1", "GS2", "GS3", "HA0", "HA1", "HA2", "HS0", "HS1", "HS2"]:
+        for n, H, W in ((1, 64, 64), (4, 256, 320), (1, 720, 1280), (2, 2048, 4096)):
+            if fits.get(layer, N in (128, 192)):
+                layer_route(layer, n, H, W, 1, N, M, precision)
+            else:
+                with pytest.raises(LicError) as e:
+                    layer_route(layer, n, H, W, 1, N, M, precision)
+                assert e.value.code == -1
+
+
+def test_routes_of_the_gdn_layers_are_all_found():
+    """The sweep that the GPU tests run sees each kernel of each form."""
+    seen = {}
+    for kind, N, M, p, layers in MODELS:
+        for layer in layers:
+            if layer in GDN:
+                seen.setdefault((N, p), set()).update(t[0] for t in routes(kind, N, M, p, layer))
+    for N, p in seen:
+        want = {"staged", "window", "split"} | ({"two_pass"} if p == 0 else set()) | ({"image"} if N == 128 else {"direct"})
+        if (N, p) == (192, 0):
+            want.discard("window")                # (no window kernel on split operands at 192 channels)
+        assert seen[N, p] == want, (N, p)
