@@ -4,7 +4,8 @@ the outputs whose window holds it.
 
 References take the operands as the form rounds them, so what is left is FP32
 accumulation (1e-4 of max |ref|) and one rounding of a stored bf16 (2^-8) or e4m3
-(2^-4) output.
+(2^-4) output.  The FP32 GDN layers are also held to what their parts leave of
+single products (test_fp32_gdn_single_products).
 """
 import numpy as np
 import pytest
@@ -158,4 +159,81 @@ def test_a_nan_reaches_its_window(kind, N, M, prec, layer):
         what = f"{layer} {t} at {n} x {H} x {W}"
         assert bool(got[reached].isnan().all()), what
         assert torch.equal(got[~reached].view(torch.uint8), out[~reached].view(torch.uint8)), what
+    c.close()
+
+
+# ---- FP32 GDN layers: what the parts leave of single products
+#
+# Convolution weights on the diagonal of the centre tap only and two active
+# channels a pixel (the image layer: one pixel in each output's window, and two
+# channels that answer to each tap): an output is one product x = w v, and its
+# n = beta + gamma_a x_a^2 + gamma_b x_b^2 with x_b about 2^-12 x_a.  In units u = 2^-24 of
+# the value: a value is its three bf16 parts exactly (8 + 8 + 8 bits); of a product's
+# nine part products the (1, 2), (2, 1) and (2, 2) are left out, 2.004, and the sum
+# rounds once: x is 3.02 off.  n: x_a^2 carries 2 x 3.02 + 1, its product with gamma
+# 3.02, the additions 2.3 (the small parts round far below): 12.4, half of it
+# under the root; the root is good to 1 ulp (2), the last product rounds (1):
+# 3.02 + 6.2 + 3 = 12.2.  A part left out of weights, pixels, gamma or squares, or one of
+# the six products, costs up to 2^-16 = 256 u (half that under the root).
+BOUND = 12.5
+
+
+def single_products_model(kind, N, M, seed):
+    rng = np.random.default_rng(seed)
+    P = dict(synth.model_params(kind, N, M, gamma="dense"))
+    for layer in ("ga1", "ga2", "gs1", "gs2", "gs0", "ga0"):
+        w = np.zeros_like(P[layer + ".w"])
+        d = min(w.shape[0], w.shape[1])
+        if layer == "ga0":
+            for ch, u, v in np.ndindex(3, 5, 5):
+                pair = rng.choice(w.shape[0], 2, replace=False)
+                w[pair, ch, u, v] = (1 + rng.random(2)) * rng.choice([-1, 1], 2) * [1.0, 2.0 ** -12]
+        else:
+            w[np.arange(d), np.arange(d), 2, 2] = (1 + rng.random(d)) * rng.choice([-1, 1], d)
+        P[layer + ".w"] = w.astype(np.float32).astype(w.dtype)
+        P[layer + ".b"] = np.zeros_like(P[layer + ".b"])
+        P[layer + ".beta"] = np.full_like(P[layer + ".beta"], 2.0 ** -10)
+        P[layer + ".gamma"] = (1 + rng.random(P[layer + ".gamma"].shape)).astype(np.float32).astype(P[layer + ".gamma"].dtype)
+    return P
+
+
+@pytest.mark.parametrize("kind,N,M,layer", [(1, N, M, layer) for N, M in ((128, 192), (192, 320))
+                                             for layer in ("GA0", "GA1", "GA2", "GS1", "GS2")] + [(2, 128, 192, "GS0")])
+def test_fp32_gdn_single_products(kind, N, M, layer):
+    import torch
+    P = single_products_model(kind, N, M, N + M)
+    c = codec(kind, N, M, FP32, P)
+    name, up = layer.lower(), layer[1] == "S"
+    w, beta, gamma = (torch.from_numpy(np.asarray(P[name + k], np.float64)).cuda() for k in (".w", ".beta", ".gamma"))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    todo = {("image", "f32x"): (1, 320, 448)} if layer == "GA0" else routes(kind, N, M, FP32, layer)
+    for t, (n, H, W) in todo.items():
+        if layer == "GA0":
+            x = torch.zeros((n, 3, H, W), device="cuda")
+            for ch in range(3):                                # pixels 6 apart, of either parity, one colour each
+                for oy, ox in ((2, 18 * ch + 2), (H // 2 + 1, 18 * ch + 5)):
+                    y, xx = torch.arange(oy, oy + H // 2 - 6, 6, device="cuda"), torch.arange(ox, W - 3, 54, device="cuda")
+                    x[:, ch, y[:, None], xx] = 1 + torch.rand((n, len(y), len(xx)), device="cuda", generator=g)
+            out = torch.empty((n, H // 2, W // 2, N), device="cuda")
+            c.run_layer(layer, n, H, W, x, out)
+            conv = conv64(torch, x.double().permute(0, 2, 3, 1).contiguous(), w, torch.zeros(N, dtype=torch.float64, device="cuda"))
+            assert int((conv != 0).sum(3).max()) == 2
+        else:
+            hi, wi, ho, wo = grids(layer, H, W)
+            ci = M if layer == "GS0" else N
+            a = torch.randint(0, N, (n, hi, wi, 2), device="cuda", generator=g)
+            v = (1 + torch.rand((n, hi, wi, 2), device="cuda", generator=g)) * torch.tensor([1.0, 2.0 ** -12], device="cuda")
+            x = torch.zeros((n, hi, wi, ci), device="cuda").scatter_(3, a, v)
+            out = torch.empty((n, ho, wo, N), device="cuda")
+            c.run_layer(layer, n, H, W, x, out)
+            diag = torch.diagonal(w[:, :, 2, 2])[:N]
+            conv = (x if up else x[:, ::2, ::2])[..., :N].double() * diag
+        norm = (beta + (conv * conv).view(-1, N) @ gamma.t().contiguous()).sqrt().view(conv.shape)
+        ref = conv * norm if up else conv / norm
+        got = out[:, ::2, ::2] if up else out
+        on = ref != 0
+        err = float(((got.double() - ref).abs() / ref.abs())[on].max()) * 2 ** 24
+        assert err <= BOUND, f"{layer} {t} at {n} x {H} x {W}: {err:.2f} x 2^-24"
+        assert bool((got[~on] == 0).all())
     c.close()
