@@ -37,10 +37,10 @@ struct LayerGPU {
     float out_q = 8.0f;                // e4m3 activations out hold out_q x the value
     float in_scale = 1.0f;             // e4m3 form: 1 / out_q of the layer whose e4m3 output this reads
     std::vector<float> wsc;            // e4m3 form: per packed row, the weight scale
-    std::vector<PhaseDesc> host_ph;
     PhaseDesc* d_ph = nullptr;
+    // operands, each only where a kernel of the layer reads it (layer_operands)
     uint8_t* d_w = nullptr;            // packed weights (float, bf16 or e4m3)
-    uint16_t* d_wx = nullptr;          // FP32 GDN layers: the same as three bf16 parts (ConvArgs::wx)
+    uint16_t* d_wx = nullptr;          // FP32 image layer at 192 channels: the same as three bf16 parts (ConvArgs::wx)
     uint8_t* d_wt = nullptr;           // weights in fragment order (ConvArgs::wt, ws)
     uint8_t* d_ws = nullptr;
     uint16_t* d_gt = nullptr;          // gamma in fragment order (ConvArgs::gt)

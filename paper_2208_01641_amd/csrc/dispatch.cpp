@@ -236,6 +236,23 @@ int choose_route(const ConvShape& L, const ConvArgs& a, long policy_pixels, Conv
     return LIC_OK;
 }
 
+Operands layer_operands(const ConvShape& L)
+{
+    Operands o{};
+    if (L.ep == EP_GDN || L.ep == EP_IGDN) {
+        const bool direct = L.ld == LD_RGB && !image_available(L.cop, L.dt == DT_F32 ? DT_F32X : L.dt);
+        o.w = direct && L.dt != DT_F32;
+        o.wx = direct && L.dt == DT_F32;
+        o.gsplit = direct;
+        o.ws = o.gt = !direct;
+        o.wt = L.ld != LD_RGB;
+    } else {
+        o.w = L.ep != EP_RGB;                           // grids large enough for unsplit K
+        o.ws = true;
+    }
+    return o;
+}
+
 int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipStream_t s, std::string* errp,
                        KernelKey* chosen)
 {

@@ -86,6 +86,11 @@ struct ConvRoute {
 // slots, comes from policy_pixels, the pixel grid of one image, so that results
 // do not depend on the batch.  Returns a lic_status; *errp names the failure.
 int choose_route(const ConvShape& L, const ConvArgs& a, long policy_pixels, ConvRoute* r, std::string* errp);
+// The operand layouts that the kernels of a layer read at any size (ConvArgs).
+struct Operands {
+    bool w, wx, wt, ws, gsplit, gt;
+};
+Operands layer_operands(const ConvShape& L);
 // Chooses and launches (sets a.ncog, a.tw).  With chosen non-null nothing is
 // launched: the route's key is stored there.
 int launch_conv_policy(const ConvShape& L, ConvArgs& a, long policy_pixels, hipStream_t s, std::string* errp,

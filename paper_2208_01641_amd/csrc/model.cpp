@@ -5,6 +5,8 @@
 
 #include <algorithm>
 #include <cmath>
+#include <system_error>
+#include <thread>
 
 #include "codec.h"
 #include "packing.h"
@@ -103,6 +105,23 @@ uint16_t bf16_rne(float f)
     if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
     u += 0x7fffu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
+}
+
+// Eight floats as three bf16 parts, each rounded to nearest from what the
+// previous ones leave: part g at out + g pitch.
+static void split_parts8(const float* v, uint16_t* out, size_t pitch)
+{
+    for (int e = 0; e < 8; ++e) {
+        float rem = v[e];
+        for (int g = 0; g < 3; ++g) {
+            const uint16_t h = bf16_rne(rem);
+            out[g * pitch + e] = h;
+            const uint32_t u = (uint32_t)h << 16;
+            float hv;
+            memcpy(&hv, &u, 4);
+            rem -= hv;
+        }
+    }
 }
 
 // GDN gamma [co][co] (row-major, FP64 from the weight blob, used as FP32)
@@ -281,7 +300,21 @@ int Codec::load(const void* blob, size_t len)
     norm = cfg.norm;
     lanes = cfg.rans_lanes;
     S = cfg.y_slices;
-    model_id = fnv1a(blob, len);
+    // The model id, a serial hash of every byte (two fifths of a create's time),
+    // beside the rest; joined on every way out.
+    struct Hash {
+        std::thread t;
+        ~Hash()
+        {
+            if (t.joinable()) t.join();
+        }
+    } hash;
+    auto take_id = [this, blob, len] { model_id = fnv1a(blob, len); };
+    try {
+        hash.t = std::thread(take_id);
+    } catch (const std::system_error&) {
+        take_id();
+    }
 
     // entropy model: per-channel medians, factorized and Gaussian tables
     std::vector<uint32_t> ff, gf;
@@ -501,6 +534,10 @@ int Codec::build_layers(const ParamMap& P)
     if (!thr.empty()) HIP_TRY(hipMemcpy(d_thr, thr.data(), 63 * sizeof(float), hipMemcpyHostToDevice));
     (void)C;
 
+    // (kept from layer to layer: fresh pages cost more than the packing)
+    std::vector<float> wp;
+    std::vector<uint16_t> hb, hx;                        // bf16 / split-FP32 / e4m3 operands
+    std::vector<uint8_t> h8, wt;
     for (const LayerSpec& sp : layer_specs(kind)) {
         LayerGPU& L = layers[sp.id];
         auto wit = P.find(std::string(sp.name) + ".w");
@@ -553,20 +590,18 @@ int Codec::build_layers(const ParamMap& P)
             return LIC_E_MODEL;
         }
 
+        const Operands use = layer_operands(shape);
         const size_t total = pm.idx.size();
-        const size_t esz = L.dt == DT_BF16 ? 2 : L.dt == DT_FP8 ? 1 : 4;
-        L.d_w = (uint8_t*)dev_alloc(total * esz);
-        L.d_ph = (PhaseDesc*)dev_alloc(ph.size() * sizeof(PhaseDesc));
-        L.d_bias = (float*)dev_alloc(L.cop * sizeof(float));
-        if (!L.d_w || !L.d_ph || !L.d_bias) { err = "device allocation failed"; return LIC_E_NOMEM; }
-        std::vector<float> wp(total);
-        std::vector<uint16_t> hb, hx;                    // bf16 / split-FP32 / e4m3 operands
-        std::vector<uint8_t> h8;
+        auto upload = [&](const void* src, size_t bytes) -> uint8_t* {
+            void* dst = dev_alloc(bytes);
+            if (dst && hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) != hipSuccess) dst = nullptr;
+            return static_cast<uint8_t*>(dst);
+        };
+        wp.resize(total);
         for (size_t j = 0; j < total; ++j) wp[j] = pm.idx[j] < 0 ? 0.0f : (float)w[pm.idx[j]];
         if (L.dt == DT_BF16) {
             hb.resize(total);
             for (size_t j = 0; j < total; ++j) hb[j] = bf16_rne(wp[j]);
-            HIP_TRY(hipMemcpy(L.d_w, hb.data(), total * esz, hipMemcpyHostToDevice));
         } else if (L.dt == DT_FP8) {
             // per packed row: scale = max |w| / 448 over every tap and phase
             // of the row, w8 = e4m3(w / scale); the epilogue multiplies by
@@ -594,74 +629,47 @@ int Codec::build_layers(const ParamMap& P)
             if (!L.d_rscale) { err = "device allocation failed"; return LIC_E_NOMEM; }
             const int rc = upload_rscale(L);
             if (rc != LIC_OK) return rc;
-            HIP_TRY(hipMemcpy(L.d_w, h8.data(), total, hipMemcpyHostToDevice));
-        } else {
-            HIP_TRY(hipMemcpy(L.d_w, wp.data(), total * esz, hipMemcpyHostToDevice));
-            if (sp.ep == EP_GDN || sp.ep == EP_IGDN) {
-                // split-FP32 operands of the whole-frame kernels: each group of
-                // 8 packed values as [part 0 x8][part 1 x8][part 2 x8], the
-                // parts rounded to nearest from what the previous ones leave
-                if (total % 8 != 0) { err = std::string("packing mismatch in ") + sp.name; return LIC_E_MODEL; }
-                hx.resize(3 * total);
-                for (size_t j = 0; j < total; ++j) {
-                    float rem = wp[j];
-                    for (int g = 0; g < 3; ++g) {
-                        const uint16_t h = bf16_rne(rem);
-                        hx[24 * (j / 8) + 8 * g + j % 8] = h;
-                        const uint32_t u = (uint32_t)h << 16;
-                        float hv;
-                        memcpy(&hv, &u, 4);
-                        rem -= hv;
-                    }
-                }
-                if (sp.ld == LD_RGB) {                  // (the others have them in fragment order only)
-                    L.d_wx = (uint16_t*)dev_alloc(hx.size() * sizeof(uint16_t));
-                    if (!L.d_wx) { err = "device allocation failed"; return LIC_E_NOMEM; }
-                    HIP_TRY(hipMemcpy(L.d_wx, hx.data(), hx.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
-                }
-            }
         }
         for (size_t i = 0; i < ph.size(); ++i) ph[i].woff = (int64_t)pm.off[i];
-        // the same operands in fragment order: of the staged kernels (GDN layers;
-        // FP32 as bf16 parts) and of the split-K kernels
-        auto fragments = [&](int form, uint8_t** dst) -> int {
-            const TileOrder to = tile_order(pm, form);
-            const size_t es = form == DT_F32 ? 4 : form == DT_FP8 ? 1 : 2, sub = form == DT_F32X ? 3 : 1;
-            std::vector<uint8_t> wt(to.idx.size() * es);
-            for (size_t j = 0; j < to.idx.size(); ++j) {
-                const int32_t x = to.idx[j];
-                if (form == DT_FP8) {
-                    wt[j] = x < 0 ? 0 : h8[x];
-                } else if (form == DT_F32) {
-                    memcpy(&wt[4 * j], &wp[x], 4);
-                } else {
-                    const uint16_t v = form == DT_BF16 ? hb[x] : hx[24 * (x / 8) + 8 * ((j / 512) % 3) + x % 8];
-                    memcpy(&wt[2 * j], &v, 2);
-                }
-            }
-            *dst = (uint8_t*)dev_alloc(wt.size());
-            if (!*dst) { err = "device allocation failed"; return LIC_E_NOMEM; }
-            HIP_TRY(hipMemcpy(*dst, wt.data(), wt.size(), hipMemcpyHostToDevice));
-            for (size_t i = 0; i < ph.size(); ++i) ph[i].wtoff = (int64_t)(to.off[i] / sub);
-            return LIC_OK;
-        };
-        if (sp.ld == LD_RGB) {
-            const int rc = fragments(L.dt == DT_F32 ? DT_F32X : L.dt, &L.d_ws);
-            if (rc != LIC_OK) return rc;
-        } else {
-            const bool gdn = sp.ep == EP_GDN || sp.ep == EP_IGDN;
-            int rc = LIC_OK;
-            if (gdn) rc = fragments(L.dt == DT_F32 ? DT_F32X : L.dt, &L.d_wt);
-            if (rc == LIC_OK && gdn && L.dt != DT_F32) L.d_ws = L.d_wt;
-            else if (rc == LIC_OK) rc = fragments(L.dt, &L.d_ws);
-            if (rc != LIC_OK) return rc;
+        // Each layout only where a kernel of this layer reads it: row-major (the
+        // direct kernel), and the same operands in fragment order, of the staged,
+        // window and image kernels (FP32 as bf16 parts) and of the split-K ones.
+        const void* const packed = L.dt == DT_BF16 ? (const void*)hb.data() : L.dt == DT_FP8 ? (const void*)h8.data() : wp.data();
+        const size_t esz = L.dt == DT_BF16 ? 2 : L.dt == DT_FP8 ? 1 : 4;
+        bool up = true;
+        if (use.w) up = (L.d_w = upload(packed, total * esz)) != nullptr;
+        if (total % 8 != 0) { err = std::string("packing mismatch in ") + sp.name; return LIC_E_MODEL; }
+        if (up && use.wx) {                              // each group of 8 values as [part 0 x8][part 1 x8][part 2 x8]
+            hx.resize(3 * total);
+            for (size_t j = 0; j < total; j += 8) split_parts8(&wp[j], &hx[3 * j], 8);
+            up = (L.d_wx = (uint16_t*)upload(hx.data(), hx.size() * sizeof(uint16_t))) != nullptr;
         }
-        HIP_TRY(hipMemcpy(L.d_ph, ph.data(), ph.size() * sizeof(PhaseDesc), hipMemcpyHostToDevice));
-        L.host_ph = ph;
+        auto fragments = [&](int form) -> uint8_t* {
+            const TileOrder to = tile_order(pm, form);
+            static const uint8_t zeros[16] = {};
+            wt.resize(to.run.size() * (form == DT_F32X ? 48 : 16));
+            for (size_t j = 0; j < to.run.size(); ++j) {
+                const size_t x = (size_t)to.run[j];
+                if (form == DT_F32X)                     // the lane's 16 bytes of three fragments
+                    split_parts8(&wp[x], reinterpret_cast<uint16_t*>(&wt[(j / 64) * 3072 + (j % 64) * 16]), 512);
+                else
+                    memcpy(&wt[16 * j], to.run[j] < 0 ? zeros : static_cast<const uint8_t*>(packed) + x * esz, 16);
+            }
+            for (size_t i = 0; i < ph.size(); ++i) ph[i].wtoff = (int64_t)to.off[i];
+            return upload(wt.data(), wt.size());
+        };
+        const int staged_form = L.dt == DT_F32 ? DT_F32X : L.dt;
+        if (up && use.wt) up = (L.d_wt = fragments(staged_form)) != nullptr;
+        if (up && use.ws) {
+            const int form = sp.ld == LD_RGB ? staged_form : L.dt;
+            L.d_ws = use.wt && form == staged_form ? L.d_wt : fragments(form);
+            up = L.d_ws != nullptr;
+        }
+        if (up) up = (L.d_ph = (PhaseDesc*)upload(ph.data(), ph.size() * sizeof(PhaseDesc))) != nullptr;
         std::vector<float> bias(L.cop, 0.0f);
         for (int r = 0; r < L.cop; ++r)
             if (pm.bias_idx[r] >= 0) bias[r] = (float)b[pm.bias_idx[r]];
-        HIP_TRY(hipMemcpy(L.d_bias, bias.data(), L.cop * sizeof(float), hipMemcpyHostToDevice));
+        if (up) up = (L.d_bias = (float*)upload(bias.data(), L.cop * sizeof(float))) != nullptr;
 
         if (sp.ep == EP_GDN || sp.ep == EP_IGDN) {
             auto git = P.find(std::string(sp.name) + ".gamma");
@@ -674,16 +682,14 @@ int Codec::build_layers(const ParamMap& P)
             if (co % 32 != 0) { err = std::string("GDN layers need a multiple of 32 channels: ") + sp.name; return LIC_E_MODEL; }
             const std::vector<uint16_t> g = gdn_gamma_split(git->second.second, co);
             std::vector<float> be(beit->second.second.begin(), beit->second.second.end());
-            L.d_gsplit = (uint16_t*)dev_alloc(g.size() * sizeof(uint16_t));
-            L.d_beta = (float*)dev_alloc(be.size() * sizeof(float));
-            if (!L.d_gsplit || !L.d_beta) { err = "device allocation failed"; return LIC_E_NOMEM; }
-            HIP_TRY(hipMemcpy(L.d_gsplit, g.data(), g.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
-            HIP_TRY(hipMemcpy(L.d_beta, be.data(), be.size() * sizeof(float), hipMemcpyHostToDevice));
-            const std::vector<uint16_t> gt = gdn_gamma_tiles(g, co, L.dt == DT_F32 ? 3 : 2);
-            L.d_gt = (uint16_t*)dev_alloc(gt.size() * sizeof(uint16_t));
-            if (!L.d_gt) { err = "device allocation failed"; return LIC_E_NOMEM; }
-            HIP_TRY(hipMemcpy(L.d_gt, gt.data(), gt.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+            if (up) up = (L.d_beta = (float*)upload(be.data(), be.size() * sizeof(float))) != nullptr;
+            if (up && use.gsplit) up = (L.d_gsplit = (uint16_t*)upload(g.data(), g.size() * sizeof(uint16_t))) != nullptr;
+            if (up && use.gt) {
+                const std::vector<uint16_t> gt = gdn_gamma_tiles(g, co, L.dt == DT_F32 ? 3 : 2);
+                up = (L.d_gt = (uint16_t*)upload(gt.data(), gt.size() * sizeof(uint16_t))) != nullptr;
+            }
         }
+        if (!up) { err = std::string("device allocation or upload failed: ") + sp.name; return LIC_E_NOMEM; }
         // offsets: quantisation of y (factorized: channel medians; hyperprior: 0)
         // and of z (medians); dequantisation in the loaders likewise
         if (sp.id == LIC_GA3) L.d_qmu = kind == 0 ? d_medians : d_zero;

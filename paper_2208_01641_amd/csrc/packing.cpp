@@ -170,23 +170,22 @@ TileOrder tile_order(const PackMap& m, int dt)
     TileOrder o;
     const int kch = dt == DT_F32 ? 16 : dt == DT_FP8 ? 128 : 32;
     const int ke = dt == DT_F32 ? 4 : dt == DT_FP8 ? 16 : 8;      // elements per 16 bytes
-    const int sub = dt == DT_F32X ? 3 : dt == DT_FP8 ? 2 : 1;
-    o.idx.reserve((m.idx.size() + m.ph.size() * (size_t)kch * m.cop) * sub / (dt == DT_FP8 ? 2 : 1));
+    const int sub = dt == DT_FP8 ? 2 : 1;
     for (size_t f = 0; f < m.ph.size(); ++f) {
-        o.off.push_back(o.idx.size());
+        o.off.push_back(o.run.size() * ke);
         const int ntaps = m.ph[f].ntaps;
         const int nk = dt == DT_FP8 ? (ntaps * m.cin + kch - 1) / kch : ntaps * (m.cin / kch);
+        o.run.reserve(o.run.size() + (size_t)nk * (m.cop / 16) * sub * 64);
         for (int k = 0; k < nk; ++k)
             for (int mt = 0; mt < m.cop / 16; ++mt)
                 for (int s = 0; s < sub; ++s)
                     for (int l = 0; l < 64; ++l) {
-                        // the first of the lane's elements (16 e4m3 elements are of one tap)
+                        // (16 e4m3 elements are of one tap)
                         const int x = k * kch + (l / 16) * 32 + s * 16;
                         const int t = dt == DT_FP8 ? x / m.cin : k % ntaps;
                         const int c = dt == DT_FP8 ? x % m.cin : (k / ntaps) * kch + (l / 16) * ke;
                         const size_t j = m.off[f] + ((size_t)t * m.cop + mt * 16 + l % 16) * m.cin + c;
-                        for (int e = 0; e < ke; ++e)
-                            o.idx.push_back(t < ntaps ? (int32_t)(j + e) : -1);
+                        o.run.push_back(t < ntaps ? (int32_t)j : -1);
                     }
     }
     return o;

@@ -55,11 +55,12 @@ PackMap pack_map_checkerboard(int ci, int co, int k, int part, bool pair_rows);
 // Chunks run channel slice outer, tap inner (e4m3: over the flattened (tap,
 // channel) axis, zero past its end); lane l holds row l % 16 of the block and
 // the elements of lane group l / 16.  sub: the three bf16 parts of split-FP32,
-// the two 16-byte halves of e4m3, else one.  Returns for every element its
-// index in the packed array (e4m3 past the end: -1; split-FP32: the FP32
-// element, once per part) and the element offset of each phase.
+// the two 16-byte halves of e4m3, else one.  Returns for every 16 bytes the index
+// in the packed array of the first element, the others follow it there
+// (split-FP32: of the eight FP32 elements, once for the three parts; e4m3 past the
+// end: -1); and the element offset of each phase.
 struct TileOrder {
-    std::vector<int32_t> idx;
+    std::vector<int32_t> run;
     std::vector<size_t> off;
 };
 TileOrder tile_order(const PackMap& m, int dt);
