@@ -4,14 +4,16 @@
 // part products of order <= 2 on the bf16 matrix cores), bf16, and OCP e4m3
 // with per-row FP32 scales (v_mfma_scale_f32_16x16x128_f8f6f4).
 //
-// One kernel template covers every layer of the analysis / synthesis and
-// hyper transforms (strided 5x5 and 3x3 convolutions, and stride-2 5x5
-// transposed convolutions split into sub-pixel phases), with the element-wise
-// work of each layer fused into its loader and epilogue:
+// One kernel template for strided 5x5 and 3x3 convolutions and stride-2 5x5
+// transposed convolutions split into sub-pixel phases, with the element-wise work
+// of each layer fused into its loader and epilogue.  It runs the distilled
+// synthesis network, the image layer at 192 channels, and the codec's other layers
+// without GDN on frames so large that K need not be split; the other kernels of
+// the codec keep its products and the order of its sums:
 //   loaders  : float NHWC, |float| NHWC (h_a input), int8 symbols + per-channel
 //              offset (dequantisation of y_hat / z_hat), and the 3-channel NCHW
 //              image with the 64-multiple zero padding done by bounds checks.
-//   epilogues: bias, ReLU, GDN / IGDN or 1DN (channel-mixing sum of x^2, or
+//   epilogues: bias, ReLU, GDN or 1DN (channel-mixing sum of x^2, or
 //              of |x| for 1DN, as a second MFMA contraction on the registers
 //              of the first), quantisation to
 //              int8 symbols, scale-table index, and the final clamp + crop.
@@ -28,13 +30,11 @@
 // The other forms keep that arrangement with 32 channels per chunk (bf16,
 // split-FP32) or 128 (tap, channel) pairs (e4m3).
 //
-// Data movement: the GDN layers of whole frames are in gdn_kernels.hip; of
-// them only the image layer runs here (split-FP32: each K chunk's weight tile
-// goes through an LDS ring, and the gamma slices of the epilogue likewise).
-// The stride-1 output layer stages halo tiles (a block's rows of
+// Data movement: the image layer's weight tiles (split-FP32) and gamma slices go
+// through an LDS ring.  The distilled network's stride-1 output layer stages halo tiles (a block's rows of
 // pixels with a one-pixel border) and the weights in LDS per channel slice.
 // Small grids split K over the waves of a block with a fixed-order LDS
-// reduction (the codec's layers: split_kernels.hip).
+// reduction (the distilled network; the codec's layers: split_kernels.hip).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -115,7 +115,8 @@ conv_igemm(ConvArgs a)
     // every wave of the block has the same pix0 and leaves together
     // (GDN blocks of four unsplit waves keep idle waves: they take part in the
     // barriers of the shared weight and gamma staging)
-    constexpr bool kGLds = KSPLIT == 1 && WAVES == 4 && (EP == EP_GDN || EP == EP_IGDN);
+    static_assert(EP != EP_IGDN, "g_s's GDN layers: gdn_kernels.hip, window_kernels.hip, split_kernels.hip");
+    constexpr bool kGLds = KSPLIT == 1 && WAVES == 4 && EP == EP_GDN;
     // the split-FP32 form stages the (three times larger) weight tiles of its
     // GDN layers in LDS: a 2-stage ring filled from one register set (other
     // shapes would load them per wave)
@@ -839,7 +840,7 @@ conv_igemm(ConvArgs a)
         }
     };
 
-    if constexpr (EP == EP_GDN || EP == EP_IGDN) {
+    if constexpr (EP == EP_GDN) {
         // n = beta + gamma (x*x) (1DN: beta + gamma |x|): [Co x Co] x [Co x
         // pixels] on the bf16 matrix cores with FP32 accumulation.  x*x (|x|)
         // and gamma are each split into
@@ -950,16 +951,12 @@ conv_igemm(ConvArgs a)
                 f4 y;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    // GDN: x times the hardware reciprocal square root, IGDN:
-                    // x times the hardware square root (each within about one
-                    // ulp; n >= beta > 0; the correctly rounded sqrtf costs a
+                    // x times the hardware reciprocal square root (within about
+                    // one ulp; n >= beta > 0; the correctly rounded sqrtf costs a
                     // dozen more instructions per value); 1DN: x times the
-                    // hardware reciprocal (about one ulp), inverse x n
+                    // hardware reciprocal (about one ulp)
                     const float nv = nacc[mt][nt][i];
-                    if (EP == EP_GDN)
-                        y[i] = acc[mt][nt][i] * (a.norm1 ? __builtin_amdgcn_rcpf(nv) : __builtin_amdgcn_rsqf(nv));
-                    else
-                        y[i] = acc[mt][nt][i] * (a.norm1 ? nv : __builtin_amdgcn_sqrtf(nv));
+                    y[i] = acc[mt][nt][i] * (a.norm1 ? __builtin_amdgcn_rcpf(nv) : __builtin_amdgcn_rsqf(nv));
                 }
                 if (pv[nt]) store_act(obase[nt] + mt * 16 + kg * 4, y);
             }

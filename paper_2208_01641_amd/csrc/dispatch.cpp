@@ -133,7 +133,8 @@ bool route_split(const ConvShape& L, const ConvArgs& a, const Grid& g, ConvRoute
         // [360], 21 [720].
         sk.nt = 2;
     } else if (L.cop % 64 != 0 || blocks(4, 1) < 448) {
-        sk.mt = L.cop % 32 == 0 && (blocks(2, 1) >= 200 || r->key.ksplit != 8) ? 2 : 1;
+        // (eight slots: four take at least 512 tiles of 64 x 32)
+        sk.mt = L.cop % 32 == 0 && blocks(2, 1) >= 200 ? 2 : 1;
     }
     if (!split_available(sk)) return false;
     r->kernel = two_pass ? ConvRoute::TWO_PASS : ConvRoute::SPLIT;

@@ -411,14 +411,15 @@ struct GdnEntry {
 #define LIC_GB(TAG, EP)                                                                                        \
     LIC_G(TAG, 128, 8, 2, 4, 4, LD_F32, EP, DT_BF16), LIC_G(TAG, 128, 8, 1, 4, 4, LD_F32, EP, DT_BF16),        \
         LIC_G(TAG, 192, 12, 2, 4, 3, LD_F32, EP, DT_BF16), LIC_G(TAG, 192, 12, 1, 4, 4, LD_F32, EP, DT_BF16)
+// (e4m3 at 128 channels: unsplit K comes with two tiles a wave, but for GA2)
 #define LIC_GF(TAG, EP)                                                                                        \
-    LIC_G(TAG, 128, 8, 2, 4, 2, LD_F32, EP, DT_FP8), LIC_G(TAG, 128, 8, 1, 4, 3, LD_F32, EP, DT_FP8),          \
-        LIC_G(TAG, 192, 12, 2, 4, 2, LD_F32, EP, DT_FP8), LIC_G(TAG, 192, 12, 1, 4, 2, LD_F32, EP, DT_FP8)
+    LIC_G(TAG, 128, 8, 2, 4, 2, LD_F32, EP, DT_FP8), LIC_G(TAG, 192, 12, 2, 4, 2, LD_F32, EP, DT_FP8), LIC_G(TAG, 192, 12, 1, 4, 2, LD_F32, EP, DT_FP8)
 
 static const GdnEntry kGdn[] = {
     LIC_GX(LIC_GA1, EP_GDN), LIC_GX(LIC_GA2, EP_GDN), LIC_GX(LIC_GS1, EP_IGDN), LIC_GX(LIC_GS2, EP_IGDN),
     LIC_GB(LIC_GA1, EP_GDN), LIC_GB(LIC_GA2, EP_GDN), LIC_GB(LIC_GS1, EP_IGDN), LIC_GB(LIC_GS2, EP_IGDN),
-    LIC_GF(LIC_GA1, EP_GDN), LIC_GF(LIC_GA2, EP_GDN), LIC_GF(LIC_GS1, EP_IGDN), LIC_GF(LIC_GS2, EP_IGDN),
+    LIC_GF(LIC_GA1, EP_GDN), LIC_GF(LIC_GA2, EP_GDN), LIC_G(LIC_GA2, 128, 8, 1, 4, 3, LD_F32, EP_GDN, DT_FP8),
+    LIC_GF(LIC_GS1, EP_IGDN), LIC_GF(LIC_GS2, EP_IGDN),
     LIC_GK(LIC_GA1, EP_GDN), LIC_GK(LIC_GA2, EP_GDN), LIC_GK(LIC_GS1, EP_IGDN), LIC_GK(LIC_GS2, EP_IGDN),
     LIC_G4(LIC_GS0, 192, 8, 4, LD_I8, EP_IGDN, DT_BF16), LIC_G4(LIC_GS0, 192, 8, 4, LD_F32, EP_IGDN, DT_BF16),
     LIC_G4(LIC_GS0, 320, 12, 4, LD_I8, EP_IGDN, DT_BF16),

@@ -630,16 +630,17 @@ struct SplitEntry {
 
 #define LIC_S(MT, NT, RG, KS, P, WPS, LD, EP, DT) \
     {{MT, NT, RG, KS, LD, EP, DT}, conv_split<MT, NT, RG, KS, P, WPS, LD, EP, DT>}
-// 64-row tiles of 32 and 16 pixels, 32- and 16-row tiles of 16 pixels
+// Eight slots: 64-row tiles of 32 and 16 pixels, 32- and 16-row tiles of 16 pixels.
+// Four slots, which take at least 512 tiles of 64 x 32 an image: 64-row tiles, in
+// the reduced forms of 32 pixels.
 #define LIC_SE(LD, EP, DT)                                                                                    \
     LIC_S(4, 2, 1, 8, 2, 4, LD, EP, DT), LIC_S(4, 1, 1, 8, 4, 4, LD, EP, DT), LIC_S(2, 1, 1, 8, 4, 6, LD, EP, DT), \
-        LIC_S(1, 1, 1, 8, 4, 8, LD, EP, DT), LIC_S(4, 2, 1, 4, 2, 4, LD, EP, DT), LIC_S(4, 1, 1, 4, 4, 4, LD, EP, DT), \
-        LIC_S(2, 1, 1, 4, 4, 6, LD, EP, DT)
+        LIC_S(1, 1, 1, 8, 4, 8, LD, EP, DT), LIC_S(4, 2, 1, 4, 2, 4, LD, EP, DT)
+#define LIC_SE4(LD, EP, DT) LIC_SE(LD, EP, DT), LIC_S(4, 1, 1, 4, 4, 4, LD, EP, DT)
 // (e4m3 fragments are twice as large)
 #define LIC_SEF(LD, EP, DT)                                                                                   \
     LIC_S(4, 2, 1, 8, 2, 2, LD, EP, DT), LIC_S(4, 1, 1, 8, 2, 2, LD, EP, DT), LIC_S(2, 1, 1, 8, 2, 2, LD, EP, DT), \
-        LIC_S(1, 1, 1, 8, 4, 4, LD, EP, DT), LIC_S(4, 2, 1, 4, 2, 2, LD, EP, DT), LIC_S(4, 1, 1, 4, 2, 2, LD, EP, DT), \
-        LIC_S(2, 1, 1, 4, 2, 2, LD, EP, DT)
+        LIC_S(1, 1, 1, 8, 4, 4, LD, EP, DT), LIC_S(4, 2, 1, 4, 2, 2, LD, EP, DT)
 // GDN layers: 128 and 192 rows; 32-pixel tiles in FP32 only (the reduced forms
 // leave for the staged kernel before)
 #define LIC_SG(LD, EP)                                                                                        \
@@ -652,10 +653,11 @@ struct SplitEntry {
 #define LIC_SS(LD) LIC_S(1, 1, 1, 4, 8, 4, LD, EP_NONE, DT_F32)
 
 static const SplitEntry kSplit[] = {
-    LIC_SS(LD_F32), LIC_SS(LD_I8), LIC_S(2, 1, 1, 4, 4, 4, LD_I8, EP_NONE, DT_F32),
-    LIC_SE(LD_F32, EP_RELU, DT_F32),  LIC_SE(LD_F32_ABS, EP_RELU, DT_F32), LIC_SE(LD_I8, EP_RELU, DT_F32),
-    LIC_SE(LD_F32, EP_QUANT, DT_F32), LIC_SE(LD_F32, EP_QUANT, DT_BF16),   LIC_SEF(LD_F32, EP_QUANT, DT_FP8),
-    LIC_SE(LD_F32, EP_INDEX, DT_F32), LIC_SE(LD_F32, EP_NONE, DT_F32),     LIC_SE(LD_F32, EP_MSCALE, DT_F32),
+    LIC_SS(LD_F32), LIC_S(2, 1, 1, 4, 4, 6, LD_F32, EP_NONE, DT_F32),
+    LIC_SS(LD_I8), LIC_S(2, 1, 1, 4, 4, 4, LD_I8, EP_NONE, DT_F32),
+    LIC_SE4(LD_F32, EP_RELU, DT_F32),  LIC_SE4(LD_F32_ABS, EP_RELU, DT_F32), LIC_SE4(LD_I8, EP_RELU, DT_F32),
+    LIC_SE4(LD_F32, EP_QUANT, DT_F32), LIC_SE(LD_F32, EP_QUANT, DT_BF16),    LIC_SEF(LD_F32, EP_QUANT, DT_FP8),
+    LIC_SE4(LD_F32, EP_INDEX, DT_F32), LIC_SE4(LD_F32, EP_NONE, DT_F32),     LIC_SE4(LD_F32, EP_MSCALE, DT_F32),
     LIC_SG(LD_F32, EP_GDN),  LIC_SG(LD_F32, EP_IGDN),  LIC_SG(LD_I8, EP_IGDN),
     LIC_SGB(LD_F32, EP_GDN), LIC_SGB(LD_F32, EP_IGDN), LIC_SGB(LD_I8, EP_IGDN),
     LIC_SGF(LD_F32, EP_GDN), LIC_SGF(LD_F32, EP_IGDN),

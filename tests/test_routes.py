@@ -75,6 +75,22 @@ def test_every_size_has_a_kernel_and_sums_do_not_depend_on_the_batch(kind, N, M,
                     assert (r["form"], r["ksplit"]) == (alone["form"], alone["ksplit"]), (layer, n, H, W)
 
 
+@pytest.mark.parametrize("kind,N,M,precision,layers", MODELS)
+def test_split_tiles_by_k_slots(kind, N, M, precision, layers):
+    """Four slots take at least 512 tiles of 64 x 32 an image: 64 rows, in the reduced
+    forms 32 pixels (no smaller tile is compiled for them); e4m3 GDN layers at 128
+    channels have unsplit K with two 16-pixel tiles a wave, but for GA2."""
+    for layer in layers:
+        for H in SIZES:
+            for W in SIZES:
+                for n in (1, 2, 7, 33):
+                    r = layer_route(layer, n, H, W, kind, N, M, precision)
+                    if layer not in GDN and r["kernel"] == "split" and r["ksplit"] == 4:
+                        assert r["mt"] == 4 and (r["form"] == "f32" or r["nt"] == 2), (layer, n, H, W)
+                    if r["kernel"] == "staged" and (r["form"], r["ksplit"], N) == ("fp8", 1, 128) and layer != "GA2":
+                        assert r["nt"] == 2, (layer, n, H, W)
+
+
 def test_output_layer_is_fp32():
     for N, M in ((128, 192), (192, 320)):
         assert tile(layer_route("GS3", 1, 720, 1280, 1, N, M, FP32))[:3] == ("rgb", "f32", 1)
