@@ -76,10 +76,10 @@ def layer_flops(layer, H, W, N, M, kind=1):
 
 
 def kernel_src_hash():
-    """Over every kernel source and the headers they share."""
+    """Over every kernel source, the headers they share, and the choice among them."""
     h = hashlib.sha256()
     for f in sorted(os.listdir(KERNEL_DIR)):
-        if f.endswith(".hip") or f in ("conv_args.h", "gdn_finish.h", "lds_stage.h", "mfma_common.h"):
+        if f.endswith(".hip") or f in ("conv_args.h", "gdn_finish.h", "lds_stage.h", "mfma_common.h", "dispatch.cpp"):
             with open(os.path.join(KERNEL_DIR, f), "rb") as fh:
                 h.update(fh.read())
     return h.hexdigest()[:16]

@@ -174,7 +174,8 @@ def test_a_nan_reaches_its_window(kind, N, M, prec, layer):
 # 3.02, the additions 2.3 (the small parts round far below): 12.4, half of it
 # under the root; the root is good to 1 ulp (2), the last product rounds (1):
 # 3.02 + 6.2 + 3 = 12.2.  A part left out of weights, pixels, gamma or squares, or one of
-# the six products, costs up to 2^-16 = 256 u (half that under the root).
+# the six products, costs up to 2^-16 = 256 u (half that under the root; 62 and more
+# measured on the CPU with one of the six left out).
 BOUND = 12.5
 
 
