@@ -39,8 +39,8 @@ struct LayerGPU {
     std::vector<float> wsc;            // e4m3 form: per packed row, the weight scale
     PhaseDesc* d_ph = nullptr;
     // operands, each only where a kernel of the layer reads it (layer_operands)
-    uint8_t* d_w = nullptr;            // packed weights (float, bf16 or e4m3)
-    uint16_t* d_wx = nullptr;          // FP32 image layer at 192 channels: the same as three bf16 parts (ConvArgs::wx)
+    uint16_t* d_w = nullptr;           // image layer at 192 channels: packed weights, bf16 form
+    uint16_t* d_wx = nullptr;          // FP32 form: as three bf16 parts (ConvArgs::wx)
     uint8_t* d_wt = nullptr;           // weights in fragment order (ConvArgs::wt, ws)
     uint8_t* d_ws = nullptr;
     uint16_t* d_gt = nullptr;          // gamma in fragment order (ConvArgs::gt)

@@ -67,12 +67,13 @@ struct ConvArgs {
     void* out;
     void* aux;
     const PhaseDesc* ph;     // [nphase] (device)
-    const void* w;           // packed weights of every phase (float, bf16 or e4m3)
+    const void* w;           // packed weights of every phase, row-major (float or bf16): of the image
+                             // layer at 192 channels and the distilled network
     const void* wx;          // the same as bf16 parts for DT_F32X (or null): per 8 channels
                              // [part 0 x8][part 1 x8][part 2 x8], offsets 3 x those of w
     const void* wt;          // weights in fragment order (tile_order in packing.h) or null: of the
                              // staged GDN kernels (FP32: as bf16 parts),
-    const void* ws;          // of the split-K kernels
+    const void* ws;          // of the other layers' kernels, and the GDN layers' with split K
     const void* gt;          // gamma in fragment order (or null): [p][mt][part][lane][8] bf16, the
                              // parts of gamma[16 mt + lane%16][(2p + i/4) 16 + 4 (lane/16) + i%4]
     const void* zero;        // >= 64 zero bytes: the source of out-of-image reads

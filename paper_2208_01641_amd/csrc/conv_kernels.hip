@@ -103,7 +103,15 @@ conv_igemm(ConvArgs a)
     // back with readlane / bpermute (no memory access inside the K loop, so
     // the wait for a chunk's operands never covers the prefetched ones)
     const int tapv = lane < ntaps ? (((int)ph->dy[lane] & 0xffff) | ((int)ph->dx[lane] << 16)) : 0;
-    const WElem* __restrict__ wbase = static_cast<const WElem*>(a.w) + ph->woff * WMUL;
+    // The codec's layers read the weights in the fragment order that their split-K
+    // kernels read (the distilled network's and the image layer's are row-major):
+    // a second layout of them for the few frames that come here took up to 85% more
+    // device memory (bf16 context model 40 -> 74 MB).  Whole 1 KB fragments are no
+    // slower (layer call at 2368 x 2432, us: GA3 FP32 437 -> 404, bf16 218 -> 124, e4m3
+    // 120 -> 73; HS2 185 -> 177, context convolution 323 -> 298).
+    constexpr bool kFrag = TAG < LIC_NUM_LAYERS && LD != LD_RGB;
+    const WElem* __restrict__ wbase = kFrag ? static_cast<const WElem*>(a.ws) + ph->wtoff
+                                            : static_cast<const WElem*>(a.w) + ph->woff * WMUL;
     const int CoP = a.ncog * MT * 16;
     const int co0 = cog * MT * 16;
 
@@ -358,22 +366,25 @@ conv_igemm(ConvArgs a)
         }
     }
 
-    // DT_FP8: chunk kc of the flattened (tap, channel) axis; this lane group
-    // takes channels c .. c + 31 of tap t (t >= ntaps: past the end, zeros)
-    auto loadA8 = [&](int kc, Frag (&A)[MT]) __attribute__((always_inline)) {
-        const int f = kc * KCH + kg * KE;
-        const int t = f / CIN, c = f - (f / CIN) * CIN;
+    // weight fragments of chunk k: 1 KB each, of lane l the 16 bytes at 16 l (e4m3:
+    // two per 16 rows, zeros past the last tap)
+    auto frag_load = [&](int k, Frag (&A)[MT]) __attribute__((always_inline)) {
+        constexpr int SUB = DT == DT_FP8 ? 2 : 1;
+        const uint8_t* wp = reinterpret_cast<const uint8_t*>(wbase) + ((long)k * CoP + co0) * (SUB * 64) + lane * 16;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            // past the last tap: read the zero page (no divergent load)
-            const WElem* src = t < ntaps ? wbase + ((long)t * CoP + co0 + mt * 16 + l16) * CIN + c
-                                         : static_cast<const WElem*>(a.zero);
-            A[mt] = *reinterpret_cast<const Frag*>(src);
-        }
+        for (int mt = 0; mt < MT; ++mt)
+            if constexpr (DT == DT_FP8) {
+                const u32x4 lo = *reinterpret_cast<const u32x4*>(wp + mt * 2048), hi = *reinterpret_cast<const u32x4*>(wp + mt * 2048 + 1024);
+                A[mt] = Frag{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+            } else {
+                A[mt] = *reinterpret_cast<const Frag*>(wp + mt * 1024);
+            }
     };
     // (e4m3 operands come only from e4m3 activations: the image layer and
     // g_s's first and last layers run on bf16 operands in that form)
-    static_assert(DT != DT_FP8 || LD == LD_F32, "e4m3 operands load e4m3 activations only");
+    static_assert(DT != DT_FP8 || (LD == LD_F32 && kFrag), "e4m3 operands load e4m3 activations only");
+    // chunk kc of the flattened (tap, channel) axis: this lane group takes
+    // channels c .. c + 31 of tap t (t >= ntaps: past the end, zeros)
     auto loadB8 = [&](int kc, Frag (&B)[NT]) __attribute__((always_inline)) {
       if constexpr (DT == DT_FP8) {
         const int f = kc * KCH + kg * KE;
@@ -490,15 +501,19 @@ conv_igemm(ConvArgs a)
     };
     auto load_cursor = [&](Frag (&A)[MT], BRaw (&B)[NT]) __attribute__((always_inline)) {
         if constexpr (kCursor) {
-            const WElem* wp = wbase + (((long)cur_t * CoP + co0 + l16) * CIN + cur_kc * KCH + kg * KE) * WMUL;
+            if constexpr (kFrag) {
+                frag_load(cur_kc * ntaps + cur_t, A);
+            } else {
+                const WElem* wp = wbase + (((long)cur_t * CoP + co0 + l16) * CIN + cur_kc * KCH + kg * KE) * WMUL;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) A[mt] = *reinterpret_cast<const Frag*>(wp + (long)mt * 16 * CIN * WMUL);
+                for (int mt = 0; mt < MT; ++mt) A[mt] = *reinterpret_cast<const Frag*>(wp + (long)mt * 16 * CIN * WMUL);
+            }
             cursor_loadB(B);
         }
     };
     auto load = [&](int kk, Frag (&A)[MT], BRaw (&B)[NT]) __attribute__((always_inline)) {
         if constexpr (DT == DT_FP8) {
-            loadA8(kk, A);
+            frag_load(kk, A);
             loadB8(kk, B);
         } else if constexpr (kCursor) {
             load_cursor(A, B);

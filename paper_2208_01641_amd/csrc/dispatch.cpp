@@ -248,7 +248,6 @@ Operands layer_operands(const ConvShape& L)
         o.ws = o.gt = !direct;
         o.wt = L.ld != LD_RGB;
     } else {
-        o.w = L.ep != EP_RGB;                           // grids large enough for unsplit K
         o.ws = true;
     }
     return o;

@@ -632,12 +632,12 @@ int Codec::build_layers(const ParamMap& P)
         }
         for (size_t i = 0; i < ph.size(); ++i) ph[i].woff = (int64_t)pm.off[i];
         // Each layout only where a kernel of this layer reads it: row-major (the
-        // direct kernel), and the same operands in fragment order, of the staged,
-        // window and image kernels (FP32 as bf16 parts) and of the split-K ones.
+        // image layer at 192 channels), and the same operands in fragment order, of
+        // the staged, window and image kernels (FP32 as bf16 parts) and of the others.
         const void* const packed = L.dt == DT_BF16 ? (const void*)hb.data() : L.dt == DT_FP8 ? (const void*)h8.data() : wp.data();
         const size_t esz = L.dt == DT_BF16 ? 2 : L.dt == DT_FP8 ? 1 : 4;
         bool up = true;
-        if (use.w) up = (L.d_w = upload(packed, total * esz)) != nullptr;
+        if (use.w) up = (L.d_w = (uint16_t*)upload(packed, total * esz)) != nullptr;
         if (total % 8 != 0) { err = std::string("packing mismatch in ") + sp.name; return LIC_E_MODEL; }
         if (up && use.wx) {                              // each group of 8 values as [part 0 x8][part 1 x8][part 2 x8]
             hx.resize(3 * total);
