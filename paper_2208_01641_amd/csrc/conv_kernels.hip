@@ -105,8 +105,8 @@ conv_igemm(ConvArgs a)
     const int tapv = lane < ntaps ? (((int)ph->dy[lane] & 0xffff) | ((int)ph->dx[lane] << 16)) : 0;
     // The codec's layers read the weights in the fragment order that their split-K
     // kernels read (the distilled network's and the image layer's are row-major):
-    // a second layout of them for the few frames that come here took up to 85% more
-    // device memory (bf16 context model 40 -> 74 MB).  Whole 1 KB fragments are no
+    // a second layout of them for the few frames that come here took up to 86% more
+    // device memory (e4m3 context model 38 -> 71 MB).  Whole 1 KB fragments are no
     // slower (layer call at 2368 x 2432, us: GA3 FP32 437 -> 404, bf16 218 -> 124, e4m3
     // 120 -> 73; HS2 185 -> 177, context convolution 323 -> 298).
     constexpr bool kFrag = TAG < LIC_NUM_LAYERS && LD != LD_RGB;

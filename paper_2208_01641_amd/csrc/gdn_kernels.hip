@@ -4,12 +4,12 @@
 // What bounds the direct form: the MFMA operand layout puts 16 pixels in 16
 // neighbouring lanes, so a gather straight into registers sends 64 lanes to
 // 64 separate 16-byte pieces, and the vector memory path takes one piece a
-// clock (measured 15.8 bytes a clock and CU, against 61 when the four lanes
+// clock (measured 16.0 bytes a clock and CU, against 62.6 when the four lanes
 // of a quad read one 64-byte run).  Here every global load is such a run:
 //   * weights are packed in fragment order (lane by lane, 1 KB per fragment),
 //     so a chunk's weight tile goes from memory to LDS linearly and is read
-//     back linearly (LDS reads at 220 bytes a clock; 64-byte rows padded to 80
-//     bytes gave 124);
+//     back linearly (LDS reads at 235 bytes a clock; 64-byte rows padded to 80
+//     bytes gave 125);
 //   * a wave loads its pixels' channel runs with consecutive lanes on one
 //     pixel; the 16-byte pieces of a row are stored rotated by the pixel
 //     index (an exclusive or), which makes the fragment reads conflict-free

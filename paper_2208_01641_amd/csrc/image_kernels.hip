@@ -16,9 +16,8 @@
 // Products and sums are those of conv_igemm: k = (5 u + v) 3 + c in three
 // chunks of 32, then n = beta + gamma (x*x).
 //
-// 720p, kernel time (us), before -> now: split-FP32 107 -> 79 (matrix cores busy
-// about two thirds; the last 126 MB of output leave L2 after the last wave),
-// bf16 74 -> 42, e4m3 76 -> 48.
+// 720p, kernel time (us), before -> now: split-FP32 107 -> 77 (matrix cores busy
+// 43% of it; 127 MB of output), bf16 74 -> 42, e4m3 76 -> 48.
 #include <hip/hip_runtime.h>
 
 #include "../../include/lic.h"
