@@ -49,8 +49,8 @@ template <> struct Prec<DT_BF16> {
 //            to nearest from what the previous parts leave: v = v0 + v1 + v2
 //            up to 2^-27 |v|); the products of parts i + j <= 2 run on
 //            v_mfma_f32_16x16x32_bf16 (each exact in FP32) with FP32
-//            accumulation, so a product carries a relative error near
-//            2^-25, the level of FP32 rounding.  Weights are split on the host
+//            accumulation, so a product is at most 3 x 2^-24 off (2 of it what
+//            the products left out can hold), most near 2^-25.  Weights are split on the host
 //            ([part][8] per 8 channels), activations stay FP32 and are split
 //            when a chunk is used.
 struct Split3 {
